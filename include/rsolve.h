@@ -94,10 +94,11 @@ enum rs_mem { RS_MEM_HOST = 0, RS_MEM_DEVICE = 1 };
  * SpMV shapes and reduction modes change only the summation order of the
  * dot products fused into the SpMVs (the last bits of alpha and omega). */
 enum rs_option {
-    RS_OPT_SWEEP_TILES = 0,  /* 1: one launch per triangular sweep, row tiles wait only on the
-                                tiles they depend on; 0: one launch per level.  Default: 0 for
+    RS_OPT_SWEEP_TILES = 0,  /* 1: one launch per triangular sweep, rows wait only on the
+                                rows they depend on; 0: one launch per level.  Default: 0 for
                                 graph colouring (few wide levels), 1 otherwise */
-    RS_OPT_SWEEP_GRID = 1,   /* workgroups of a single-launch sweep (default 1024) */
+    RS_OPT_SWEEP_GRID = 1,   /* most workgroups of a single-launch sweep (default 1024; never more
+                                than 256, one a compute unit, are launched) */
     RS_OPT_POLL_CHUNK = 2,   /* BiCGStab iterations queued between host polls of convergence (default 1) */
     RS_OPT_USE_GRAPH = 3,    /* 1 (default): an iteration is captured once as a HIP graph and replayed.
                                 A capture is invalidated by device-synchronising calls (hipFree,
@@ -119,7 +120,7 @@ enum rs_option {
     RS_OPT_SPIN_LIMIT = 8,   /* polls before a single-launch sweep's dependency wait gives up
                                 (default 4194304, >= 0).  A wait that gives up lets its tile go
                                 on, so the launch still ends; the solve then returns RS_HIP_ERROR
-                                and the handle's sweep counters and tile flags are reset, so the
+                                and the handle's sweep counters and marks are reset, so the
                                 next call starts clean.  A small value forces that error path
                                 (for tests of the recovery) */
     RS_OPT_FUSE_SPMV = 9,    /* 1 (default): where the rows without lower blocks are the first rows

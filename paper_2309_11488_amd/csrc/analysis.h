@@ -81,13 +81,8 @@ struct Schedule {
     // i - fuse_n0.
     int y_in = 0;
     // row tiles of the single-launch sweeps: tile t covers schedule
-    // positions [start[t], start[t+1]) inside one level, and must wait for
-    // the tiles dep[dep_ptr[t] .. dep_ptr[t+1]) (earlier tiles holding rows
-    // that its rows read)
-    struct Tiles {
-        int n = 0;
-        std::vector<int32_t> start, dep_ptr, dep;
-    } ltiles, utiles;
+    // positions [ltiles[t], ltiles[t+1]) inside one level
+    std::vector<int32_t> ltiles, utiles;
 };
 
 // tile_rows: rows per sweep tile (a multiple of the rows one workgroup covers).

@@ -222,7 +222,7 @@ struct Analysis {
     DevSchedule dev{};
     DevBuf perm, prow, pcol, psrc, lrows, lptr, lcol, lsrc, ldq, l2u, upd_ptr, upd, urows, uptr, ucol, usrc, dsrc;
     DevBuf lsrc_a, usrc_a, dsrc_a, rest_dst, rest_src;
-    DevBuf lt_start, lt_dptr, lt_dep, ut_start, ut_dptr, ut_dep;
+    DevBuf lt_start, ut_start;
     // U blocks of rows with lower blocks: with FP32 factors the only U the
     // factorisation keeps in FP64 (later levels' updates read it)
     double u_kept = 0;
@@ -238,7 +238,8 @@ struct rs_ilu0 {
     DevBuf pvals, L, U, Dinv, Lf, Uf, Dinvf, bad;
     std::vector<int32_t> bad_host;
     // solve workspace
-    DevBuf work, ywork, part, spart, fpart, tickets, state, bstage, xstage, flags, ctrs;
+    DevBuf work, ywork, part, spart, fpart, tickets, state, bstage, xstage, ctrs;
+    bool y_marked = false;     // ywork holds the mark everywhere (single-launch sweeps)
     Krylov k{};
     // GMRES workspace: Krylov basis, per-system cycle state, reduction partials
     DevBuf gm_basis, gm_state, gm_part;
@@ -545,7 +546,7 @@ int bcsr_spmv(bcsr_t A, const double *x, double *y, int32_t first_sys, int32_t n
 static int build_analysis(const rs_bcsr *A, int32_t ordering, const int32_t *part, std::shared_ptr<Analysis> &out) {
     auto an = std::make_shared<Analysis>();
     an->hash = A->hash;
-    rs::build_schedule(A->n, A->nnzb, A->h_rowptr.data(), A->h_colidx.data(), ordering, an->sch, rs::kRowsPerBlock,
+    rs::build_schedule(A->n, A->nnzb, A->h_rowptr.data(), A->h_colidx.data(), ordering, an->sch, rs::kFlowRows,
                        part);
     const rs::Schedule &S = an->sch;
     for (int q = 0; q < S.n; ++q)
@@ -557,9 +558,8 @@ static int build_analysis(const rs_bcsr *A, int32_t ordering, const int32_t *par
         {&an->ldq, &S.ldq}, {&an->l2u, &S.l2u}, {&an->upd_ptr, &S.upd_ptr}, {&an->upd, &S.upd},
         {&an->urows, &S.urows}, {&an->uptr, &S.uptr}, {&an->ucol, &S.ucol}, {&an->usrc, &S.usrc},
         {&an->dsrc, &S.dsrc}, {&an->lsrc_a, &S.lsrc_a}, {&an->usrc_a, &S.usrc_a}, {&an->dsrc_a, &S.dsrc_a},
-        {&an->rest_dst, &S.rest_dst}, {&an->rest_src, &S.rest_src}, {&an->lt_start, &S.ltiles.start}, {&an->lt_dptr, &S.ltiles.dep_ptr},
-        {&an->lt_dep, &S.ltiles.dep}, {&an->ut_start, &S.utiles.start}, {&an->ut_dptr, &S.utiles.dep_ptr},
-        {&an->ut_dep, &S.utiles.dep}};
+        {&an->rest_dst, &S.rest_dst}, {&an->rest_src, &S.rest_src}, {&an->lt_start, &S.ltiles},
+        {&an->ut_start, &S.utiles}};
     // uploads on a private stream, complete before the handle is returned,
     // so that any stream may use the analysis
     hipStream_t us = nullptr;
@@ -586,9 +586,8 @@ static int build_analysis(const rs_bcsr *A, int32_t ordering, const int32_t *par
     d.nrest = (int)S.rest_dst.size();
     d.rest_dst = an->rest_dst.as<int32_t>(); d.rest_src = an->rest_src.as<int32_t>();
     d.fuse_n0 = S.fuse_n0; d.fuse_q0 = S.fuse_q0;
-    d.nlt = S.ltiles.n; d.nut = S.utiles.n;
-    d.lt_start = an->lt_start.as<int32_t>(); d.lt_dptr = an->lt_dptr.as<int32_t>(); d.lt_dep = an->lt_dep.as<int32_t>();
-    d.ut_start = an->ut_start.as<int32_t>(); d.ut_dptr = an->ut_dptr.as<int32_t>(); d.ut_dep = an->ut_dep.as<int32_t>();
+    d.nlt = (int)S.ltiles.size() - 1; d.nut = (int)S.utiles.size() - 1;
+    d.lt_start = an->lt_start.as<int32_t>(); d.ut_start = an->ut_start.as<int32_t>();
     out = std::move(an);
     return RS_OK;
 }
@@ -986,9 +985,6 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
         HIP_TRY(hipMemsetAsync(M->state.p, 0, B * sizeof(SysState), s));
         HIP_TRY(hipHostMalloc((void **)&M->h_state, B * sizeof(SysState), hipHostMallocDefault));
         HIP_TRY(hipHostMalloc((void **)&M->h_ctr, 2 * sizeof(rs::SweepCtr), hipHostMallocDefault));
-        const size_t nf = B * ((size_t)M->an->sch.ltiles.n + M->an->sch.utiles.n);
-        HIP_TRY(M->flags.alloc(nf * sizeof(int32_t)));
-        HIP_TRY(hipMemsetAsync(M->flags.p, 0, nf * sizeof(int32_t), s));
         HIP_TRY(M->ctrs.alloc(2 * sizeof(rs::SweepCtr)));
         HIP_TRY(hipMemsetAsync(M->ctrs.p, 0, 2 * sizeof(rs::SweepCtr), s));
     }
@@ -1008,20 +1004,24 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
     k.fpart_stride = fstride;
     k.lp = M->lpwork.p ? M->lpwork.as<double>() : nullptr;
     k.st = M->state.as<SysState>();
-    k.lflags = M->flags.as<int32_t>();
-    k.uflags = k.lflags + B * (size_t)M->an->sch.ltiles.n;
     k.lctr = M->ctrs.as<rs::SweepCtr>();
     k.uctr = k.lctr + 1;
+    // single-launch sweeps find y marked and leave it so; per-level sweeps
+    // store y over the marks
+    if (!M->tile_sweeps) M->y_marked = false;
+    else if (!M->y_marked) {
+        rs::launch_flow_mark(M->ywork.p, vec * sizeof(double), s);
+        HIP_TRY(hipGetLastError());
+        M->y_marked = true;
+    }
     return RS_OK;
 }
 
 // After a single-launch sweep gave up a dependency wait: clear the sweep
-// counters and every tile flag together (epochs restart from zero, so no
-// flag may keep an epoch of an earlier sweep), once the stream has drained.
+// counters and have y marked again, once the stream has drained.
 static int sweep_reset(ilu0_t M, hipStream_t s) {
-    const size_t nf = (size_t)M->batch * ((size_t)M->an->sch.ltiles.n + M->an->sch.utiles.n);
     HIP_TRY(hipMemsetAsync(M->ctrs.p, 0, 2 * sizeof(rs::SweepCtr), s));
-    if (nf) HIP_TRY(hipMemsetAsync(M->flags.p, 0, nf * sizeof(int32_t), s));
+    M->y_marked = false;
     HIP_TRY(hipStreamSynchronize(s));
     return fail(RS_HIP_ERROR, "sweep dependency wait exceeded its limit");
 }
@@ -1110,8 +1110,8 @@ static void lower_levels(ilu0_t M, const T *L, const T *D, const double *in, dou
     T *y = (T *)k.y;
     ProfScope ps(PC_LSWEEP, s, lower_bytes(M, sizeof(T), nsys), M->tile_sweeps, prof);
     if (M->tile_sweeps) {
-        rs::launch_lsweep_tiles<T>(M->an->dev, L, (size_t)S.nL * 9, in, y, vs, fuse_p, k.r, k.v, k.p, st, k.lflags,
-                                   k.lctr, nsys, M->sweep_grid, M->spin_limit, s, ps.start(), ps.stop());
+        rs::launch_lsweep_flow<T>(M->an->dev, L, (size_t)S.nL * 9, in, y, out, vs, fuse_p, k.r, k.v, k.p, st, k.lctr,
+                                  k.uctr, nsys, S.nl_levels, M->sweep_grid, M->spin_limit, s, ps.start(), ps.stop());
         return;
     }
     // the upper sweep's first level (rows without upper blocks) is finished
@@ -1176,12 +1176,12 @@ static void upper_levels(ilu0_t M, const T *U, const T *D, double *out, bool fus
                          bool lp = false) {
     const rs::Schedule &S = M->an->sch;
     const size_t vs = k.vstride;
-    const T *y = (const T *)k.y;
+    T *y = (T *)k.y;
     const double fb = (fmode != rs::FUSE_NONE ? fused_spmv_bytes(M, nsys) : 0.0) + (lp ? lp_upper_extra(M, nsys) : 0.0);
     ProfScope ps(PC_USWEEP, s, upper_bytes(M, sizeof(T), nsys) + fb, M->tile_sweeps, prof);
     if (M->tile_sweeps) {
-        rs::launch_usweep_tiles<T>(M->an->dev, U, (size_t)S.nU * 9, D, (size_t)M->n * 9, y, out, vs, st, k.uflags,
-                                   k.uctr, nsys, M->sweep_grid, M->spin_limit, s, ps.start(), ps.stop());
+        rs::launch_usweep_flow<T>(M->an->dev, U, (size_t)S.nU * 9, D, (size_t)M->n * 9, y, out, vs, st, k.uctr,
+                                  k.lctr, nsys, S.nu_levels, M->sweep_grid, M->spin_limit, s, ps.start(), ps.stop());
         return;
     }
     // the fused rows' upper launch reads their rows of A': always inside
@@ -1517,11 +1517,10 @@ int noalloc_scratch(unsigned char **out) {
 }
 
 // Carving of the workspace for n_sys systems of M: the new-order input, the
-// lower sweep's y, the new-order output (each n_sys * vstride doubles), the
-// single-launch sweeps' tile flags, and their two counters; each part
-// 256-byte aligned.
+// lower sweep's y, the new-order output (each n_sys * vstride doubles), and
+// the single-launch sweeps' two counters; each part 256-byte aligned.
 struct NoAllocLayout {
-    size_t vin, y, vout, flags, ctrs, end, nflags;
+    size_t vin, y, vout, ctrs, end;
 };
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1529,12 +1528,10 @@ size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 NoAllocLayout noalloc_layout(const rs_ilu0 *M, int n_sys) {
     NoAllocLayout l{};
     const size_t vec = align256((size_t)n_sys * rs::vec_stride(M->n) * sizeof(double));
-    l.nflags = (size_t)n_sys * ((size_t)M->an->sch.ltiles.n + M->an->sch.utiles.n);
     l.vin = 0;
     l.y = vec;
     l.vout = 2 * vec;
-    l.flags = 3 * vec;
-    l.ctrs = l.flags + align256(l.nflags * sizeof(int32_t));
+    l.ctrs = 3 * vec;
     l.end = l.ctrs + align256(2 * sizeof(rs::SweepCtr));
     return l;
 }
@@ -1563,14 +1560,14 @@ int ilu0_apply_noalloc(ilu0_t M, const double *v, double *z, int32_t first_sys, 
     k.vstride = rs::vec_stride(M->n);
     double *vin = (double *)(base + lay.vin), *vout = (double *)(base + lay.vout);
     k.y = base + lay.y;
-    k.lflags = (int32_t *)(base + lay.flags);
-    k.uflags = k.lflags + (size_t)n_sys * M->an->sch.ltiles.n;
     k.lctr = (rs::SweepCtr *)(base + lay.ctrs);
     k.uctr = k.lctr + 1;
     // the workspace keeps the last call's contents (any handle's): the
-    // sweeps' epochs start again from zero
-    if (M->tile_sweeps)
-        rs::launch_fill_u32((uint32_t *)(base + lay.flags), (lay.end - lay.flags) / sizeof(uint32_t), 0u, s);
+    // single-launch sweeps' counters and marks are set anew
+    if (M->tile_sweeps) {
+        rs::launch_fill_u32((uint32_t *)(base + lay.ctrs), (lay.end - lay.ctrs) / sizeof(uint32_t), 0u, s);
+        rs::launch_flow_mark(k.y, lay.vout - lay.y, s);
+    }
     const rs::Schedule &S = M->an->sch;
     rs::launch_permute_vec(M->an->dev.perm, v, vin, M->n, k.vstride, n_sys, false, s);
     if (M->precision == RS_PREC_FP32_FACTORS)
@@ -1590,11 +1587,8 @@ int ilu0_apply_noalloc(ilu0_t M, const double *v, double *z, int32_t first_sys, 
     rs::SweepCtr c[2];
     HIP_TRY(hipMemcpyAsync(c, k.lctr, sizeof c, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (c[0].error || c[1].error) {
-        rs::launch_fill_u32((uint32_t *)(base + lay.flags), (lay.end - lay.flags) / sizeof(uint32_t), 0u, s);
-        HIP_TRY(hipStreamSynchronize(s));
+    if (c[0].error || c[1].error)
         return fail(RS_HIP_ERROR, "ilu0_apply_noalloc: sweep dependency wait exceeded its limit");
-    }
     return RS_OK;
 }
 
@@ -2078,7 +2072,7 @@ int ilu0_autotune(ilu0_t M, bcsr_t A, const double *b, int32_t mem, double reduc
         st = time_cfg({sp0, v, 0, M->sweep_grid, 0});
         if (st != RS_OK) return st;
     }
-    for (int g : {256, 512, 1024, 2048}) {
+    for (int g : {64, 128, 256}) {
         st = time_cfg({sp0, bestc.sweep, 1, g, 0});
         if (st != RS_OK) return st;
     }

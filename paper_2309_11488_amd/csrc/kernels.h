@@ -36,7 +36,7 @@ struct DevSchedule {
     int fuse_n0, fuse_q0;
     // sweep tiles (see Schedule::Tiles)
     int nlt, nut;
-    const int32_t *lt_start, *lt_dptr, *lt_dep, *ut_start, *ut_dptr, *ut_dep;
+    const int32_t *lt_start, *ut_start;
 };
 
 // Standard wells kept separate (y -= C^T D^-1 B x for every well), as the
@@ -68,12 +68,15 @@ struct GmState {
     int32_t pad;
 };
 
-// Work counter of one single-launch sweep kernel: tickets hand out (tile,
-// system) items in dependency order; the last workgroup to leave resets the
-// tickets and publishes the epoch that marks a tile as done in this sweep.
-// error != 0 records a dependency wait that exceeded its spin limit.
+// Work counter of one single-launch sweep kernel (one 128-byte line a word):
+// the XCD that claimed the launch (1 + its id; 0: none yet), the next
+// (tile, system) item, and a word that is set when a dependency wait
+// exceeded its spin limit.  owner and ticket are zero before a launch (the
+// other sweep's launch clears them); error stays until the host clears it.
 struct SweepCtr {
-    uint32_t ticket, exit, epoch, error;
+    uint32_t owner, pad0[31];
+    uint32_t ticket, pad1[31];
+    uint32_t error, pad2[31];
 };
 
 // Workspace vectors of one solve in the new order: system k's vector starts
@@ -93,7 +96,6 @@ struct Krylov {
     size_t fpart_stride;
     double *lp;         // lower parts of the second application (k_spmv_lp): 6 values per row, 2 vstride per system, or NULL
     SysState *st;       // nsys states
-    int32_t *lflags, *uflags;  // per (system, tile): epoch of the sweep that finished it
     SweepCtr *lctr, *uctr;
 };
 
@@ -103,6 +105,7 @@ constexpr int kRowsPerWave = 21;                            // 3 lanes per block
 constexpr int kWavesPerBlock = 4;
 constexpr int kRowsPerBlock = kRowsPerWave * kWavesPerBlock;  // 84 block rows per workgroup
 constexpr int kRowThreads = kWave * kWavesPerBlock;           // 256
+constexpr int kFlowRows = 64;                                 // rows of a tile of the single-launch sweeps
 constexpr int kVecThreads = 256;
 constexpr int kVecItems = 4;                                // entries per thread per tile
 constexpr int kVecTile = kVecThreads * kVecItems;           // 1024 entries
@@ -214,18 +217,24 @@ void launch_usweep(const DevSchedule &d, const T *U, size_t u_stride, const T *D
 // dispatch records at the kernel's start and end.
 
 // Single-launch sweeps over all tiles of all nsys systems (L: lower
-// schedule, U: upper schedule).  grid = number of workgroups; spin = polls
-// before a dependency wait gives up (sets ctr->error and goes on).
+// schedule, U: upper schedule), always launched in turn, a lower then an
+// upper one: on entry to the lower sweep every entry of y holds the mark
+// (launch_flow_mark once; the upper sweep restores it) and both counters are
+// clear; next = the other sweep's counter.  levels: of the sweep's schedule;
+// grid = most workgroups; spin = polls before a dependency wait gives up
+// (sets ctr->error and goes on).
 constexpr int kSpinLimitDefault = 1 << 22;
 template <typename T>
-void launch_lsweep_tiles(const DevSchedule &d, const T *L, size_t l_stride, const double *in, T *y, size_t vstride,
-                         bool fuse_p, const double *r, const double *v, double *p, SysState *st, int32_t *flags,
-                         SweepCtr *ctr, int nsys, int grid, int spin, hipStream_t s, hipEvent_t ev0 = nullptr,
-                         hipEvent_t ev1 = nullptr);
+void launch_lsweep_flow(const DevSchedule &d, const T *L, size_t l_stride, const double *in, T *y, double *z,
+                        size_t vstride, bool fuse_p, const double *r, const double *v, double *p, SysState *st,
+                        SweepCtr *ctr, SweepCtr *next, int nsys, int levels, int grid, int spin, hipStream_t s,
+                        hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 template <typename T>
-void launch_usweep_tiles(const DevSchedule &d, const T *U, size_t u_stride, const T *Dinv, size_t d_stride,
-                         const T *y, double *z, size_t vstride, SysState *st, int32_t *flags, SweepCtr *ctr, int nsys,
-                         int grid, int spin, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_usweep_flow(const DevSchedule &d, const T *U, size_t u_stride, const T *Dinv, size_t d_stride, T *y,
+                        double *z, size_t vstride, SysState *st, SweepCtr *ctr, SweepCtr *next, int nsys, int levels,
+                        int grid, int spin, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// Fill p with the mark.
+void launch_flow_mark(void *p, size_t bytes, hipStream_t s);
 
 // Plain y = A x (rows in storage order), FP64.
 // y = A x (minus the separate wells, when w has any: t2 is computed first).

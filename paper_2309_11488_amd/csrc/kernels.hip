@@ -272,9 +272,8 @@ __device__ inline int stage_copy(const T *__restrict__ val, const int32_t *__res
 
 // acc (+|-)= sum_c val[e][r][c] * x[3 col[e] + c] over this lane's blocks
 // e in [lo, hi), all staged in LDS from `base`; blocks ascending.  The x
-// entries of up to 8 blocks are gathered before use; COH gathers them with
-// agent-coherent loads (x written by other workgroups of the same launch).
-template <bool SUB, bool COH, typename T, typename TX>
+// entries of up to 8 blocks are gathered before use.
+template <bool SUB, typename T, typename TX>
 __device__ inline T walk_pass(const T *sv, const int32_t *sc, int shift, int base, int lo, int hi, int r,
                               const TX *__restrict__ x, T acc) {
     for (int e = lo; e < hi; e += 8) {
@@ -283,9 +282,7 @@ __device__ inline T walk_pass(const T *sv, const int32_t *sc, int shift, int bas
         for (int u = 0; u < 8; ++u) {
             const int j = sc[min(e + u, hi - 1) - base];
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-                xv[u][c] = COH ? __hip_atomic_load(x + 3 * j + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                               : x[3 * j + c];
+            for (int c = 0; c < 3; ++c) xv[u][c] = x[3 * j + c];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
@@ -342,7 +339,7 @@ __device__ inline T stage_walk(const int32_t *__restrict__ ptr, const int32_t *_
         __syncthreads();
         const int shift = stage_copy<T, CAP, NT, NTL>(val, col, base, cnt, st);
         __syncthreads();
-        acc = walk_pass<SUB, false>((const T *)st.v, st.c, shift, base, max(my0, base), min(my1, base + cnt), L.r,
+        acc = walk_pass<SUB>((const T *)st.v, st.c, shift, base, max(my0, base), min(my1, base + cnt), L.r,
                                     x, acc);
     }
     return acc;
@@ -354,12 +351,9 @@ __device__ inline T stage_walk(const int32_t *__restrict__ ptr, const int32_t *_
 constexpr int kRowWavesPerEU = 5;
 
 // LDS capacity (blocks) per pass: 160 (SpMV) or 128 (per-level sweeps) per
-// wave, so a workgroup of 7-block rows copies its blocks in one pass; the
-// single-launch sweeps' tiles keep 80 per wave (more workgroups resident to
-// wait on their dependencies).
+// wave, so a workgroup of 7-block rows copies its blocks in one pass.
 constexpr int kSpmvCapPerWave = 160;
 constexpr int kSweepCapPerWave = 128;
-constexpr int kSweepCap = 4 * 80;   // single-launch sweeps: 4-wave workgroups
 
 // Row walk of a workgroup of W waves: staged through LDS or direct.
 template <int W, int STAGE, int CAPW, bool SUB, typename T, typename TX>
@@ -825,169 +819,276 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kRo
 
 // ------------------------------------------------ single-launch sweeps
 
-// Tiles are handed out by an atomic ticket in schedule order (tile-major,
-// system-minor), so a workgroup only ever waits for items with smaller
-// tickets, which are held by running workgroups: the launch cannot
-// deadlock, whatever the number of resident workgroups.  A tile first copies
-// its factor blocks into LDS (independent of the solution), then waits until
-// every tile it depends on carries this sweep's epoch, computes, writes its
-// rows with agent-coherent stores, waits for those stores to complete and
-// publishes its own flag.  Waits are bounded: past `spin` polls (the
-// handle's RS_OPT_SPIN_LIMIT) the counter's error word is set and the tile
-// proceeds (no hang).
+// A launch over all levels of a schedule whose rows wait on each other
+// through the result itself: every value a row produces is its own flag.
+// The result vector holds kMark (a NaN pattern no row stores) until its rows
+// are written; a row polls the entries it reads until none holds kMark, so a
+// dependency costs one store and one load and no other location's order
+// matters.  Bound by the length of the dependency chain, 0.68-0.75 us a level on
+// one XCD: on a 10 000-cell grid under level scheduling (63 levels) a sweep
+// takes 47 us, where tiles of rows that waited on one another's flags took
+// 125 us; on 96k cells with NNCs (1 791 levels) 1.2 ms against 3.3-3.9 ms.
+//
+// Workgroups draw (tile, system) items from an atomic ticket in schedule
+// order (tile-major, system-minor), so a row only ever waits for rows of
+// items held by running workgroups: the launch cannot deadlock, whatever the
+// number of resident workgroups.  The next ticket is drawn while the current
+// item runs.  Waits are bounded: past `spin` polls (the handle's
+// RS_OPT_SPIN_LIMIT), or once another wait has given up, the counter's error
+// word is set and the row proceeds (no hang).
+//
+// XCD: the workgroups of one XCD (the first to arrive claims the launch; the
+// others leave) share the work and its L2: results stay in that L2 and the
+// polls read it (sc0 loads: the scope of a workgroup that may be spread over
+// the CUs of an XCD).  A bare chain of dependent stores takes 0.27 us a step
+// there, against 0.54 us between XCDs with agent-scope loads and stores; one
+// XCD reads HBM at about 1.3 TB/s, so it serves schedules of narrow levels
+// (flow_one_xcd).
 
-struct TileWalk {
-    int item, tile, sys;
-};
-
-// Draw the next item for the workgroup; false when none is left.
-__device__ inline bool next_item(SweepCtr *ctr, int total, int nsys, TileWalk &w) {
-    __shared__ int s_item;
-    if (threadIdx.x == 0)
-        s_item = (int)__hip_atomic_fetch_add(&ctr->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    w.item = s_item;
-    __syncthreads();
-    if (w.item >= total) return false;
-    w.tile = w.item / nsys;
-    w.sys = w.item % nsys;
-    return true;
-}
-
-__device__ inline void leave_sweep(SweepCtr *ctr, uint32_t epoch) {
-    if (threadIdx.x == 0) {
-        const uint32_t e = __hip_atomic_fetch_add(&ctr->exit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (e == gridDim.x - 1) {
-            __hip_atomic_store(&ctr->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctr->exit, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctr->epoch, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-}
-
-__device__ inline void wait_tiles(const int32_t *__restrict__ dptr, const int32_t *__restrict__ dep,
-                                  const int32_t *flags, int tile, uint32_t epoch, SweepCtr *ctr, int spin) {
-    for (int i = dptr[tile] + threadIdx.x; i < dptr[tile + 1]; i += blockDim.x) {
-        const int32_t *f = flags + dep[i];
-        int spins = 0;
-        while ((uint32_t)__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins > spin) {
-                __hip_atomic_fetch_or(&ctr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-        }
-    }
-}
-
-// Every wave waits for its own stores, then one thread marks the tile done.
-__device__ inline void publish_tile(int32_t *flags, int tile, uint32_t epoch) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(flags + tile, (int32_t)epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <typename T, bool FUSE_P>
-__global__ void __launch_bounds__(kRowThreads) k_lsweep_tiles(DevSchedule d, const T *__restrict__ L,
-                                                              size_t l_stride, const double *__restrict__ in,
-                                                              T *__restrict__ y, size_t vstride,
-                                                              const double *__restrict__ rv,
-                                                              const double *__restrict__ vv, double *__restrict__ pv,
-                                                              SysState *__restrict__ st, int32_t *__restrict__ flags,
-                                                              SweepCtr *__restrict__ ctr, int nsys, int spin) {
-    __shared__ Stage<T, kSweepCap> sv;
-    const uint32_t epoch = __hip_atomic_load(&ctr->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-    const int total = d.nlt * nsys;
-    TileWalk w;
-    while (next_item(ctr, total, nsys, w)) {
-        if (st && st[w.sys].phase != PH_RUN) continue;
-        const int q0 = d.lt_start[w.tile], q1 = d.lt_start[w.tile + 1];
-        const RowLane rl = row_lane<kWavesPerBlock>(0, q0, q1);
-        const size_t vo = (size_t)w.sys * vstride;
-        const T *Ls = L + (size_t)w.sys * l_stride;
-        const int e0 = d.lptr[q0], e1 = d.lptr[q1];
-        const int my0 = rl.act ? d.lptr[rl.q] : 0, my1 = rl.act ? d.lptr[rl.q + 1] : 0;
-        int cnt = min(kSweepCap, e1 - e0), shift = 0;
-        if (cnt > 0) shift = stage_copy<T, kSweepCap, kRowThreads>(Ls, d.lcol, e0, cnt, sv);
-        const int i = rl.act ? d.lrows[rl.q] : 0;
-        T acc = 0;
-        if (rl.act) {
-            const size_t k = vo + 3 * (size_t)i + rl.r;
-            if (FUSE_P) {
-                const double beta = st[w.sys].beta, omega = st[w.sys].omega;
-                const double p = rv[k] + beta * (pv[k] - omega * vv[k]);
-                pv[k] = p;
-                acc = (T)p;
-            } else {
-                acc = (T)in[k];
-            }
-        }
-        wait_tiles(d.lt_dptr, d.lt_dep, flags + (size_t)w.sys * d.nlt, w.tile, epoch, ctr, spin);
-        __syncthreads();
-        for (int base = e0; base < e1; base += kSweepCap) {
-            if (base != e0) {
-                cnt = min(kSweepCap, e1 - base);
-                __syncthreads();
-                shift = stage_copy<T, kSweepCap, kRowThreads>(Ls, d.lcol, base, cnt, sv);
-                __syncthreads();
-            }
-            acc = walk_pass<true, true>((const T *)sv.v, sv.c, shift, base, max(my0, base), min(my1, base + cnt),
-                                        rl.r, y + vo, acc);
-        }
-        if (rl.act) __hip_atomic_store(y + vo + 3 * (size_t)i + rl.r, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        publish_tile(flags + (size_t)w.sys * d.nlt, w.tile, epoch);
-    }
-    leave_sweep(ctr, epoch);
-}
+constexpr uint32_t kMark = 0x7ff4beefu;   // a NaN as FP32, and twice in a row as FP64
 
 template <typename T>
-__global__ void __launch_bounds__(kRowThreads) k_usweep_tiles(DevSchedule d, const T *__restrict__ U,
-                                                              size_t u_stride, const T *__restrict__ Dinv,
-                                                              size_t d_stride, const T *__restrict__ y,
-                                                              double *__restrict__ z, size_t vstride,
-                                                              SysState *__restrict__ st, int32_t *__restrict__ flags,
-                                                              SweepCtr *__restrict__ ctr, int nsys, int spin) {
-    __shared__ Stage<T, kSweepCap> sv;
-    const uint32_t epoch = __hip_atomic_load(&ctr->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-    const int total = d.nut * nsys;
-    TileWalk w;
-    while (next_item(ctr, total, nsys, w)) {
-        if (st && st[w.sys].phase != PH_RUN) continue;
-        const int q0 = d.ut_start[w.tile], q1 = d.ut_start[w.tile + 1];
-        const RowLane rl = row_lane<kWavesPerBlock>(0, q0, q1);
-        const size_t vo = (size_t)w.sys * vstride;
-        const T *Us = U + (size_t)w.sys * u_stride;
-        const int e0 = d.uptr[q0], e1 = d.uptr[q1];
-        const int my0 = rl.act ? d.uptr[rl.q] : 0, my1 = rl.act ? d.uptr[rl.q + 1] : 0;
-        int cnt = min(kSweepCap, e1 - e0), shift = 0;
-        if (cnt > 0) shift = stage_copy<T, kSweepCap, kRowThreads>(Us, d.ucol, e0, cnt, sv);
-        const int i = rl.act ? d.urows[rl.q] : 0;
-        T acc = rl.act ? y[vo + 3 * (size_t)i + rl.r] : (T)0;
-        T dq[3] = {0, 0, 0};
-        if (rl.act) {
-            const T *dp = Dinv + (size_t)w.sys * d_stride + (size_t)rl.q * 9 + 3 * rl.r;
-            dq[0] = dp[0]; dq[1] = dp[1]; dq[2] = dp[2];
-        }
-        wait_tiles(d.ut_dptr, d.ut_dep, flags + (size_t)w.sys * d.nut, w.tile, epoch, ctr, spin);
-        __syncthreads();
-        for (int base = e0; base < e1; base += kSweepCap) {
-            if (base != e0) {
-                cnt = min(kSweepCap, e1 - base);
-                __syncthreads();
-                shift = stage_copy<T, kSweepCap, kRowThreads>(Us, d.ucol, base, cnt, sv);
-                __syncthreads();
-            }
-            acc = walk_pass<true, true>((const T *)sv.v, sv.c, shift, base, max(my0, base), min(my1, base + cnt),
-                                        rl.r, z + vo, acc);
-        }
-        const T t0 = __shfl(acc, rl.base, 64), t1 = __shfl(acc, rl.base + 1, 64), t2 = __shfl(acc, rl.base + 2, 64);
-        if (rl.act) {
-            const T zr = dot3(dq[0], dq[1], dq[2], t0, t1, t2);
-            __hip_atomic_store(z + vo + 3 * (size_t)i + rl.r, (double)zr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        publish_tile(flags + (size_t)w.sys * d.nut, w.tile, epoch);
+struct FlowBits { using type = uint64_t; static constexpr uint64_t mark = ((uint64_t)kMark << 32) | kMark; };
+template <>
+struct FlowBits<float> { using type = uint32_t; static constexpr uint32_t mark = kMark; };
+
+// The entries of a vector other rows of the launch write.  XCD loads go past
+// the CU's own cache to the XCD's L2 (aux bit 0: sc0; bit 31: volatile).
+template <typename T, bool XCD>
+struct FlowSrc {
+    using Bits = typename FlowBits<T>::type;
+    const T *p;
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ FlowSrc(const T *base, size_t count) : p(base) {
+        if constexpr (XCD)
+            rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)(count * sizeof(T)), 0x00027000);
     }
-    leave_sweep(ctr, epoch);
+    __device__ Bits load(int i) const {
+        if constexpr (!XCD)
+            return __hip_atomic_load((const Bits *)p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else if constexpr (sizeof(T) == 8)
+            return __builtin_bit_cast(Bits, __builtin_amdgcn_raw_buffer_load_b64(rsrc, i * 8, 0, (int)0x80000001));
+        else
+            return __builtin_amdgcn_raw_buffer_load_b32(rsrc, i * 4, 0, (int)0x80000001);
+    }
+};
+
+// Store a row's result where other rows poll for it (never the mark itself).
+template <bool XCD, typename T>
+__device__ inline void flow_store(T *p, T v) {
+    using Bits = typename FlowBits<T>::type;
+    Bits b = __builtin_bit_cast(Bits, v);
+    if (b == FlowBits<T>::mark) b ^= 1;
+    __hip_atomic_store((Bits *)p, b, __ATOMIC_RELAXED, XCD ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline void flow_mark(T *p) {
+    using Bits = typename FlowBits<T>::type;
+    *(Bits *)p = FlowBits<T>::mark;
+}
+
+// After a poll that found a mark: true when the wait gives up.
+__device__ inline bool flow_give_up(SweepCtr *ctr, int &spins, int spin) {
+    if (++spins > spin) {
+        __hip_atomic_store(&ctr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    }
+    if ((spins & 255) == 0 && __hip_atomic_load(&ctr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
+    if (spins > 4) __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");
+    return false;
+}
+
+// Whether the calling workgroup takes part: any workgroup, or with XCD those
+// of the XCD that claims the launch.
+template <bool XCD>
+__device__ inline bool flow_join(SweepCtr *ctr) {
+    if constexpr (!XCD) return true;
+    __shared__ int s_in;
+    if (threadIdx.x == 0) {
+        // hwreg(HW_REG_XCC_ID, 0, 4)
+        const uint32_t me = 1u + (uint32_t)__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11));
+        uint32_t own = __hip_atomic_load(&ctr->owner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (own == 0u &&
+            __hip_atomic_compare_exchange_strong(&ctr->owner, &own, me, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            own = me;
+        s_in = own == me;
+    }
+    __syncthreads();
+    return s_in != 0;
+}
+
+// Counters of the launch that comes next (the lower and the upper sweep of
+// an application alternate, so each clears the other's).
+__device__ inline void flow_clear(SweepCtr *ctr) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        __hip_atomic_store(&ctr->owner, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ctr->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// Run f(tile, system) for the workgroup's items in ticket order.  The last
+// wave draws the tickets (a partly filled tile leaves it idle).
+template <typename F>
+__device__ inline void flow_items(SweepCtr *ctr, int total, int nsys, F &&f) {
+    __shared__ int s_item[2];
+    const bool draws = threadIdx.x == kRowThreads - 64;
+    auto draw = [&]() {
+        return (int)__hip_atomic_fetch_add(&ctr->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (draws) s_item[0] = draw();
+    for (int it = 0;; it ^= 1) {
+        __syncthreads();
+        const int item = __builtin_amdgcn_readfirstlane(s_item[it]);
+        if (item >= total) return;
+        int next = 0;
+        if (draws) next = draw();
+        f(item / nsys, item % nsys);
+        if (draws) s_item[it ^ 1] = next;
+    }
+}
+
+// Lanes of the flow kernels: a quad per block row, lane r of the quad its
+// row r (lane 3 repeats row 2 and stores nothing), so a row's three values
+// are exchanged by quad permutes in the vector ALU instead of through LDS:
+// the exchange is part of every dependency.
+struct FlowLane {
+    int q, r;
+    bool own;   // stores its row's values
+};
+constexpr int kFlowRowsPerWave = 16;
+static_assert(kFlowRows == kFlowRowsPerWave * kWavesPerBlock, "a tile is one workgroup's rows");
+__device__ inline FlowLane flow_lane(int q0) {
+    FlowLane l;
+    l.q = q0 + (int)(threadIdx.x >> 2);
+    l.r = min((int)(threadIdx.x & 3), 2);
+    l.own = (threadIdx.x & 3) < 3;
+    return l;
+}
+template <int CTRL>
+__device__ inline uint32_t quad_perm(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+}
+// The value of lane K of the quad.
+template <int K, typename V>
+__device__ inline V quad_get(V v) {
+    constexpr int C = K * 0x55;
+    if constexpr (sizeof(V) == 4) {
+        return __builtin_bit_cast(V, quad_perm<C>(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const uint64_t lo = quad_perm<C>((uint32_t)b), hi = quad_perm<C>((uint32_t)(b >> 32));
+        return __builtin_bit_cast(V, lo | (hi << 32));
+    }
+}
+__device__ inline bool quad_any(bool v) {
+    uint32_t m = v ? 1u : 0u;
+    m |= quad_perm<0xb1>(m);   // lanes 1 0 3 2
+    m |= quad_perm<0x4e>(m);   // lanes 2 3 0 1
+    return m != 0u;
+}
+
+// acc -= sum_c val[e][r][c] * x[3 col[e] + c] over the blocks [lo, hi) of a
+// row, ascending, once the entries of x are there.
+template <bool XCD, typename T, typename TX>
+__device__ inline T flow_walk(const int32_t *__restrict__ col, const T *__restrict__ val, int lo, int hi, int r,
+                              const FlowSrc<TX, XCD> &x, T acc, SweepCtr *ctr, int spin) {
+    using Bits = typename FlowBits<TX>::type;
+    constexpr int NB = 4;
+    for (int e = lo; e < hi; e += NB) {
+        int j[NB];
+        T b[NB][3];
+        Bits xv[NB];
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int ee = min(e + u, hi - 1);
+            j[u] = col[ee];
+            const T *bp = val + (size_t)ee * 9 + 3 * r;
+            b[u][0] = bp[0]; b[u][1] = bp[1]; b[u][2] = bp[2];
+        }
+        int spins = 0;
+        for (;;) {
+            bool miss = false;
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (e + u < hi) xv[u] = x.load(3 * j[u] + r);
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (e + u < hi) miss |= xv[u] == FlowBits<TX>::mark;
+            if (!quad_any(miss) || flow_give_up(ctr, spins, spin)) break;
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+            if (e + u < hi) {
+                const T v = (T)__builtin_bit_cast(TX, xv[u]);
+                acc -= dot3(b[u][0], b[u][1], b[u][2], quad_get<0>(v), quad_get<1>(v), quad_get<2>(v));
+            }
+    }
+    return acc;
+}
+
+// Lower sweep: y holds the mark everywhere on entry (the upper sweep leaves
+// it so).  Marks z for the upper sweep that follows.
+template <typename T, bool FUSE_P, bool XCD>
+__global__ void __launch_bounds__(kRowThreads) k_lsweep_flow(DevSchedule d, const T *__restrict__ L,
+                                                             size_t l_stride, const double *__restrict__ in,
+                                                             T *y, double *__restrict__ z, size_t vstride,
+                                                             const double *__restrict__ rv,
+                                                             const double *__restrict__ vv, double *__restrict__ pv,
+                                                             SysState *__restrict__ st, SweepCtr *ctr,
+                                                             SweepCtr *next, int nsys, int spin) {
+    flow_clear(next);
+    if (!flow_join<XCD>(ctr)) return;
+    flow_items(ctr, d.nlt * nsys, nsys, [&](int tile, int sys) {
+        if (st && st[sys].phase != PH_RUN) return;
+        const FlowLane fl = flow_lane(d.lt_start[tile]);
+        if (fl.q >= d.lt_start[tile + 1]) return;
+        const size_t vo = (size_t)sys * vstride;
+        const size_t k = vo + 3 * (size_t)d.lrows[fl.q] + fl.r;
+        T acc;
+        if (FUSE_P) {
+            const double beta = st[sys].beta, omega = st[sys].omega;
+            const double p = rv[k] + beta * (pv[k] - omega * vv[k]);
+            if (fl.own) pv[k] = p;
+            acc = (T)p;
+        } else {
+            acc = (T)in[k];
+        }
+        if (fl.own) flow_mark(z + k);
+        const FlowSrc<T, XCD> src(y + vo, vstride);
+        acc = flow_walk<XCD>(d.lcol, L + (size_t)sys * l_stride, d.lptr[fl.q], d.lptr[fl.q + 1], fl.r, src, acc, ctr,
+                             spin);
+        if (fl.own) flow_store<XCD>(y + k, acc);
+    });
+}
+
+// Upper sweep: z holds the mark everywhere on entry.  Each row marks its own
+// y again once it has read it.
+template <typename T, bool XCD>
+__global__ void __launch_bounds__(kRowThreads) k_usweep_flow(DevSchedule d, const T *__restrict__ U,
+                                                             size_t u_stride, const T *__restrict__ Dinv,
+                                                             size_t d_stride, T *__restrict__ y, double *z,
+                                                             size_t vstride, SysState *__restrict__ st,
+                                                             SweepCtr *ctr, SweepCtr *next, int nsys, int spin) {
+    flow_clear(next);
+    if (!flow_join<XCD>(ctr)) return;
+    flow_items(ctr, d.nut * nsys, nsys, [&](int tile, int sys) {
+        if (st && st[sys].phase != PH_RUN) return;
+        const FlowLane fl = flow_lane(d.ut_start[tile]);
+        if (fl.q >= d.ut_start[tile + 1]) return;
+        const size_t vo = (size_t)sys * vstride;
+        const size_t k = vo + 3 * (size_t)d.urows[fl.q] + fl.r;
+        T acc = y[k];
+        if (fl.own) flow_mark(y + k);
+        const T *dp = Dinv + (size_t)sys * d_stride + (size_t)fl.q * 9 + 3 * fl.r;
+        const T d0 = dp[0], d1 = dp[1], d2 = dp[2];
+        const FlowSrc<double, XCD> src(z + vo, vstride);
+        acc = flow_walk<XCD>(d.ucol, U + (size_t)sys * u_stride, d.uptr[fl.q], d.uptr[fl.q + 1], fl.r, src, acc, ctr,
+                             spin);
+        const double zr = (double)dot3(d0, d1, d2, quad_get<0>(acc), quad_get<1>(acc), quad_get<2>(acc));
+        if (fl.own) flow_store<XCD>(z + k, zr);
+    });
 }
 
 // -------------------------------------------------------------------- SpMV
@@ -2079,42 +2180,77 @@ template void launch_usweep<float>(const DevSchedule &, const float *, size_t, c
                                    double *, size_t, SysState *, int, int, int, int, bool, hipStream_t, hipEvent_t,
                                    hipEvent_t);
 
+// Whether one XCD runs a flow launch.  Its dependencies cost half the time,
+// but it holds an eighth of the CUs and of the bandwidth, so it is taken
+// while the rows of a level (of all systems) are few: an application on 158
+// rows a level (10 000-cell grid) takes 127 us on one XCD and 161 us on all,
+// on 54 rows a level (96k cells with NNCs) 2 460 against 3 840, on 3 400 a
+// level (Block-Jacobi, 113k cells) 273 against 130 (with its permutations).
+// count: entries of the longest vector polled (the XCD's loads address at
+// most 2 GiB of it).
+constexpr int kFlowXcdRows = 1000;
+static bool flow_one_xcd(int n, int levels, int nsys, size_t count) {
+    return (double)n * nsys <= (double)kFlowXcdRows * levels && count * sizeof(double) < ((size_t)1 << 31);
+}
+// Workgroups of a flow launch: one a CU.  More only add polls of rows far
+// from the front (Block-Jacobi application 130 us at 256, 140 at 512, 170 at
+// 1 024; 96k cells with NNCs 2 490, 2 590 and 2 840 us).
+constexpr int kFlowGrid = 256;
+static int flow_grid(bool one_xcd, int grid, int items) {
+    grid = std::min(grid, kFlowGrid);
+    return std::max(1, one_xcd ? grid : std::min(grid, items));
+}
+
 template <typename T>
-void launch_lsweep_tiles(const DevSchedule &d, const T *L, size_t l_stride, const double *in, T *y, size_t vstride,
-                         bool fuse_p, const double *r, const double *v, double *p, SysState *st, int32_t *flags,
-                         SweepCtr *ctr, int nsys, int grid, int spin, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+void launch_lsweep_flow(const DevSchedule &d, const T *L, size_t l_stride, const double *in, T *y, double *z,
+                        size_t vstride, bool fuse_p, const double *r, const double *v, double *p, SysState *st,
+                        SweepCtr *ctr, SweepCtr *next, int nsys, int levels, int grid, int spin, hipStream_t s,
+                        hipEvent_t ev0, hipEvent_t ev1) {
     if (d.nlt <= 0 || nsys <= 0) return;
-    grid = std::max(1, std::min(grid, d.nlt * nsys));
-    if (fuse_p)
-        launch_ev(k_lsweep_tiles<T, true>, dim3(grid), dim3(kRowThreads), s, ev0, ev1, d, L, l_stride, in, y,
-                  vstride, r, v, p, st, flags, ctr, nsys, spin);
-    else
-        launch_ev(k_lsweep_tiles<T, false>, dim3(grid), dim3(kRowThreads), s, ev0, ev1, d, L, l_stride, in, y,
-                  vstride, r, v, p, st, flags, ctr, nsys, spin);
+    const bool one = flow_one_xcd(d.n, levels, nsys, vstride);
+    const dim3 g(flow_grid(one, grid, d.nlt * nsys));
+    auto go = [&](auto kern) {
+        launch_ev(kern, g, dim3(kRowThreads), s, ev0, ev1, d, L, l_stride, in, y, z, vstride, r, v, p, st, ctr, next,
+                  nsys, spin);
+    };
+    if (fuse_p) {
+        if (one) go(k_lsweep_flow<T, true, true>); else go(k_lsweep_flow<T, true, false>);
+    } else {
+        if (one) go(k_lsweep_flow<T, false, true>); else go(k_lsweep_flow<T, false, false>);
+    }
 }
 
 template <typename T>
-void launch_usweep_tiles(const DevSchedule &d, const T *U, size_t u_stride, const T *Dinv, size_t d_stride,
-                         const T *y, double *z, size_t vstride, SysState *st, int32_t *flags, SweepCtr *ctr, int nsys,
-                         int grid, int spin, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+void launch_usweep_flow(const DevSchedule &d, const T *U, size_t u_stride, const T *Dinv, size_t d_stride, T *y,
+                        double *z, size_t vstride, SysState *st, SweepCtr *ctr, SweepCtr *next, int nsys, int levels,
+                        int grid, int spin, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     if (d.nut <= 0 || nsys <= 0) return;
-    grid = std::max(1, std::min(grid, d.nut * nsys));
-    launch_ev(k_usweep_tiles<T>, dim3(grid), dim3(kRowThreads), s, ev0, ev1, d, U, u_stride, Dinv, d_stride, y, z,
-              vstride, st, flags, ctr, nsys, spin);
+    const bool one = flow_one_xcd(d.n, levels, nsys, vstride);
+    const dim3 g(flow_grid(one, grid, d.nut * nsys));
+    auto go = [&](auto kern) {
+        launch_ev(kern, g, dim3(kRowThreads), s, ev0, ev1, d, U, u_stride, Dinv, d_stride, y, z, vstride, st, ctr,
+                  next, nsys, spin);
+    };
+    if (one) go(k_usweep_flow<T, true>); else go(k_usweep_flow<T, false>);
 }
 
-template void launch_lsweep_tiles<double>(const DevSchedule &, const double *, size_t, const double *, double *,
-                                          size_t, bool, const double *, const double *, double *, SysState *,
-                                          int32_t *, SweepCtr *, int, int, int, hipStream_t, hipEvent_t, hipEvent_t);
-template void launch_lsweep_tiles<float>(const DevSchedule &, const float *, size_t, const double *, float *,
-                                         size_t, bool, const double *, const double *, double *, SysState *,
-                                         int32_t *, SweepCtr *, int, int, int, hipStream_t, hipEvent_t, hipEvent_t);
-template void launch_usweep_tiles<double>(const DevSchedule &, const double *, size_t, const double *, size_t,
-                                          const double *, double *, size_t, SysState *, int32_t *, SweepCtr *, int,
-                                          int, int, hipStream_t, hipEvent_t, hipEvent_t);
-template void launch_usweep_tiles<float>(const DevSchedule &, const float *, size_t, const float *, size_t,
-                                         const float *, double *, size_t, SysState *, int32_t *, SweepCtr *, int,
+template void launch_lsweep_flow<double>(const DevSchedule &, const double *, size_t, const double *, double *,
+                                         double *, size_t, bool, const double *, const double *, double *, SysState *,
+                                         SweepCtr *, SweepCtr *, int, int, int, int, hipStream_t, hipEvent_t,
+                                         hipEvent_t);
+template void launch_lsweep_flow<float>(const DevSchedule &, const float *, size_t, const double *, float *, double *,
+                                        size_t, bool, const double *, const double *, double *, SysState *,
+                                        SweepCtr *, SweepCtr *, int, int, int, int, hipStream_t, hipEvent_t,
+                                        hipEvent_t);
+template void launch_usweep_flow<double>(const DevSchedule &, const double *, size_t, const double *, size_t,
+                                         double *, double *, size_t, SysState *, SweepCtr *, SweepCtr *, int, int,
                                          int, int, hipStream_t, hipEvent_t, hipEvent_t);
+template void launch_usweep_flow<float>(const DevSchedule &, const float *, size_t, const float *, size_t, float *,
+                                        double *, size_t, SysState *, SweepCtr *, SweepCtr *, int, int, int, int,
+                                        hipStream_t, hipEvent_t, hipEvent_t);
+void launch_flow_mark(void *p, size_t bytes, hipStream_t s) {
+    launch_fill_u32((uint32_t *)p, bytes / sizeof(uint32_t), kMark, s);
+}
 
 // ev0 / ev1 (optional): events the dispatch itself records at the SpMV
 // kernel's start and end (kernel time only, no launch overhead).
