@@ -238,7 +238,7 @@ struct rs_ilu0 {
     DevBuf pvals, L, U, Dinv, Lf, Uf, Dinvf, bad;
     std::vector<int32_t> bad_host;
     // solve workspace
-    DevBuf work, ywork, part, spart, fpart, tickets, state, bstage, xstage, ctrs;
+    DevBuf work, ywork, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
     bool y_marked = false;     // ywork holds the mark everywhere (single-launch sweeps)
     Krylov k{};
     // GMRES workspace: Krylov basis, per-system cycle state, reduction partials
@@ -771,6 +771,11 @@ static bool reads_u(const rs_ilu0 *M, bool fused) {
     return M->tile_sweeps || (M->precision == RS_PREC_FP32_FACTORS && !fused);
 }
 
+static void factor_message(int status) {
+    g_err = status == RS_ZERO_PIVOT ? "ilu0_factor: singular pivot block"
+                                    : "ilu0_factor: a row's dependency wait exceeded its limit";
+}
+
 // The result of the handle's last factorisation, which has completed and
 // whose first singular pivots (new numbering) are in bad_host: device time,
 // per-system bad rows (original numbering, -1 when none), status.
@@ -780,16 +785,19 @@ static int factor_result(ilu0_t M, int32_t *bad_row) {
     M->factor_ms = hipEventElapsedTime(&ms, M->ev_f0, M->ev_f1) == hipSuccess ? ms : 0.0;
     int worst = RS_OK;
     M->bad_orig.assign(B, -1);
+    bool gave_up = false;
     for (size_t i = 0; i < B; ++i) {
         const int32_t b = M->bad_host[i];
+        if (b == rs::kBadWait) gave_up = true;
         const int32_t orig = (b >= 0 && b < M->n) ? M->an->sch.perm[b] : -1;
         M->bad_orig[i] = orig;
         if (orig >= 0) worst = RS_ZERO_PIVOT;
     }
+    if (gave_up) worst = RS_HIP_ERROR;
     if (bad_row) std::copy(M->bad_orig.begin(), M->bad_orig.end(), bad_row);
     M->factor_status = worst;
     M->factor_pending = false;
-    if (worst != RS_OK) g_err = "ilu0_factor: singular pivot block";
+    if (worst != RS_OK) factor_message(worst);
     return worst;
 }
 
@@ -808,6 +816,8 @@ static int check_pair(ilu0_t M, bcsr_t A) {
     if (M->batch != A->batch) return fail(RS_PATTERN_MISMATCH, "batch size differs from the analysed matrix");
     return RS_OK;
 }
+
+constexpr int kFlowFactorRows = 12000;   // see ilu0_factor
 
 int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *bad_row) {
     int st = check_pair(M, A);
@@ -831,8 +841,16 @@ int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *ba
     if (!M->ev_f0) HIP_TRY(hipEventCreate(&M->ev_f0));
     if (!M->ev_f1) HIP_TRY(hipEventCreate(&M->ev_f1));
     HIP_TRY(hipEventRecord(M->ev_f0, s));
-    HIP_TRY(hipMemsetAsync(M->bad.p, 0x7f, B * sizeof(int32_t), s));
     const size_t per = (size_t)M->nnzb * 9;
+    // One launch over all levels while a level holds few rows (of all
+    // systems): a launch per level costs 11-12 us whatever its size, a level
+    // inside the one launch 1.5-4 us, but that launch keeps one workgroup a
+    // CU, so wide levels leave the memory idle in it.  33 levels of 3 400
+    // rows (Block-Jacobi, 113k cells) take 135 instead of 414 us, four of
+    // 24 000 (96k cells, colouring) 94 instead of 84.
+    const bool flow = (double)M->n * M->batch <= (double)kFlowFactorRows * S.nl_levels && S.nl_levels > 2;
+    if (flow) HIP_TRY(M->fctr.alloc(sizeof(rs::SweepCtr)));
+    else HIP_TRY(hipMemsetAsync(M->bad.p, 0x7f, B * sizeof(int32_t), s));
     {
         // algorithmic bytes of the method: every block of the
         // preconditioner's matrix read, updated in place and written once
@@ -841,8 +859,6 @@ int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *ba
         const double bytes = 148.0 * S.nnz_m + 144.0 * (double)S.rest_dst.size();
         ProfScope ps(PC_FACTOR, s, B * bytes);
         const DevSchedule &d = M->an->dev;
-        rs::launch_gather_pairs(A->vals.as<double>(), per, M->pvals.as<double>(), per, d.rest_dst, d.rest_src,
-                                d.nrest, M->batch, s);
         const bool f32 = precision == RS_PREC_FP32_FACTORS;
         // the U of the fused rows is their rows of A', which their upper
         // launches read instead (filled in later for a consumer of U)
@@ -850,7 +866,17 @@ int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *ba
         // a first level made of those rows is a copy and a pivot inversion
         const bool first = S.fuse_n0 > 0 && S.nl_levels > 0 && S.lset[1] == S.fuse_n0 && S.lconsec[0] &&
                            S.rest_dst.empty();
-        for (int l = 0; l < S.nl_levels; ++l) {
+        if (flow)
+            rs::launch_factor_flow(d, A->vals.as<double>(), per, M->pvals.as<double>(), M->L.as<double>(),
+                                   M->U.as<double>(), M->Dinv.as<double>(), f32 ? M->Lf.as<float>() : nullptr,
+                                   f32 ? M->Uf.as<float>() : nullptr, f32 ? M->Dinvf.as<float>() : nullptr,
+                                   M->bad.as<int32_t>(), skip_u0,
+                                   std::find(S.lnarrow.begin(), S.lnarrow.end(), 0) == S.lnarrow.end(), S.nl_levels,
+                                   M->fctr.as<rs::SweepCtr>(), M->batch, s);
+        else
+            rs::launch_gather_pairs(A->vals.as<double>(), per, M->pvals.as<double>(), per, d.rest_dst, d.rest_src,
+                                    d.nrest, M->batch, s);
+        for (int l = 0; !flow && l < S.nl_levels; ++l) {
             if (l == 0 && first) {
                 rs::launch_factor_first(d, A->vals.as<double>(), per, M->pvals.as<double>(), M->Dinv.as<double>(),
                                         f32 ? M->Dinvf.as<float>() : nullptr, M->bad.as<int32_t>(), M->batch, s);
@@ -887,7 +913,7 @@ int ilu0_factor_status(ilu0_t M, int32_t *bad_row) {
         return factor_result(M, bad_row);
     }
     if (bad_row) std::copy(M->bad_orig.begin(), M->bad_orig.end(), bad_row);
-    if (M->factor_status != RS_OK) g_err = "ilu0_factor: singular pivot block";
+    if (M->factor_status != RS_OK) factor_message(M->factor_status);
     return M->factor_status;
 }
 

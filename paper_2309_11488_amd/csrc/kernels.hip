@@ -421,9 +421,14 @@ __device__ inline double inv3_row(const double (&a)[9], int r, double (&inv)[3])
     const double c01 = a[5] * a[6] - a[3] * a[8];
     const double c02 = a[3] * a[7] - a[4] * a[6];
     const double det = a[0] * c00 + a[1] * c01 + a[2] * c02;
-    if (r == 0) { inv[0] = c00 / det; inv[1] = (a[2] * a[7] - a[1] * a[8]) / det; inv[2] = (a[1] * a[5] - a[2] * a[4]) / det; }
-    else if (r == 1) { inv[0] = c01 / det; inv[1] = (a[0] * a[8] - a[2] * a[6]) / det; inv[2] = (a[2] * a[3] - a[0] * a[5]) / det; }
-    else { inv[0] = c02 / det; inv[1] = (a[1] * a[6] - a[0] * a[7]) / det; inv[2] = (a[0] * a[4] - a[1] * a[3]) / det; }
+    // one set of products and quotients for the lanes of all three rows
+    // (a branch per row runs its three divisions after the other rows')
+    const double x0 = r == 0 ? a[2] : (r == 1 ? a[0] : a[1]), x1 = r == 0 ? a[7] : (r == 1 ? a[8] : a[6]);
+    const double x2 = r == 0 ? a[1] : (r == 1 ? a[2] : a[0]), x3 = r == 0 ? a[8] : (r == 1 ? a[6] : a[7]);
+    const double y1 = r == 0 ? a[5] : (r == 1 ? a[3] : a[4]), y3 = r == 0 ? a[4] : (r == 1 ? a[5] : a[3]);
+    inv[0] = (r == 0 ? c00 : (r == 1 ? c01 : c02)) / det;
+    inv[1] = (x0 * x1 - x2 * x3) / det;
+    inv[2] = (x2 * y1 - x0 * y3) / det;
     return det;
 }
 
@@ -824,10 +829,10 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kRo
 // The result vector holds kMark (a NaN pattern no row stores) until its rows
 // are written; a row polls the entries it reads until none holds kMark, so a
 // dependency costs one store and one load and no other location's order
-// matters.  Bound by the length of the dependency chain, 0.68-0.75 us a level on
+// matters.  Bound by the length of the dependency chain, about 0.5 us a level on
 // one XCD: on a 10 000-cell grid under level scheduling (63 levels) a sweep
-// takes 47 us, where tiles of rows that waited on one another's flags took
-// 125 us; on 96k cells with NNCs (1 791 levels) 1.2 ms against 3.3-3.9 ms.
+// takes 38 us, where tiles of rows that waited on one another's flags took
+// 125 us; on 96k cells with NNCs (1 791 levels) 0.9 ms against 3.3-3.9 ms.
 //
 // Workgroups draw (tile, system) items from an atomic ticket in schedule
 // order (tile-major, system-minor), so a row only ever waits for rows of
@@ -838,12 +843,12 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kRo
 // word is set and the row proceeds (no hang).
 //
 // XCD: the workgroups of one XCD (the first to arrive claims the launch; the
-// others leave) share the work and its L2: results stay in that L2 and the
-// polls read it (sc0 loads: the scope of a workgroup that may be spread over
-// the CUs of an XCD).  A bare chain of dependent stores takes 0.27 us a step
-// there, against 0.54 us between XCDs with agent-scope loads and stores; one
-// XCD reads HBM at about 1.3 TB/s, so it serves schedules of narrow levels
-// (flow_one_xcd).
+// others leave) share the work and its L2: plain stores go through a CU's
+// own cache to that L2, where the polls (agent-scope loads, past the CU's
+// cache) find them, instead of on to memory.  A bare chain of dependent
+// stores takes 0.27 us a step there, against 0.54 us between XCDs with
+// agent-scope stores; one XCD reads HBM at about 1.3 TB/s, so it serves
+// schedules of narrow levels (flow_one_xcd).
 
 constexpr uint32_t kMark = 0x7ff4beefu;   // a NaN as FP32, and twice in a row as FP64
 
@@ -852,26 +857,11 @@ struct FlowBits { using type = uint64_t; static constexpr uint64_t mark = ((uint
 template <>
 struct FlowBits<float> { using type = uint32_t; static constexpr uint32_t mark = kMark; };
 
-// The entries of a vector other rows of the launch write.  XCD loads go past
-// the CU's own cache to the XCD's L2 (aux bit 0: sc0; bit 31: volatile).
-template <typename T, bool XCD>
-struct FlowSrc {
-    using Bits = typename FlowBits<T>::type;
-    const T *p;
-    __amdgpu_buffer_rsrc_t rsrc;
-    __device__ FlowSrc(const T *base, size_t count) : p(base) {
-        if constexpr (XCD)
-            rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)(count * sizeof(T)), 0x00027000);
-    }
-    __device__ Bits load(int i) const {
-        if constexpr (!XCD)
-            return __hip_atomic_load((const Bits *)p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else if constexpr (sizeof(T) == 8)
-            return __builtin_bit_cast(Bits, __builtin_amdgcn_raw_buffer_load_b64(rsrc, i * 8, 0, (int)0x80000001));
-        else
-            return __builtin_amdgcn_raw_buffer_load_b32(rsrc, i * 4, 0, (int)0x80000001);
-    }
-};
+// An entry of a vector other rows of the launch write.
+template <typename T>
+__device__ inline typename FlowBits<T>::type flow_load(const T *p) {
+    return __hip_atomic_load((const typename FlowBits<T>::type *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Store a row's result where other rows poll for it (never the mark itself).
 template <bool XCD, typename T>
@@ -887,15 +877,16 @@ __device__ inline void flow_mark(T *p) {
     *(Bits *)p = FlowBits<T>::mark;
 }
 
-// After a poll that found a mark: true when the wait gives up.
+// After a poll of a wave that found a mark: true when the wait gives up.
+// Polls come without a pause at first and every 64 clocks later, which
+// leaves the memory pipeline to the rows at the front.
 __device__ inline bool flow_give_up(SweepCtr *ctr, int &spins, int spin) {
     if (++spins > spin) {
         __hip_atomic_store(&ctr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return true;
     }
     if ((spins & 255) == 0 && __hip_atomic_load(&ctr->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
-    if (spins > 4) __builtin_amdgcn_s_sleep(1);
-    asm volatile("" ::: "memory");
+    if (spins > 64) __builtin_amdgcn_s_sleep(1);
     return false;
 }
 
@@ -968,7 +959,7 @@ __device__ inline FlowLane flow_lane(int q0) {
 }
 template <int CTRL>
 __device__ inline uint32_t quad_perm(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
 }
 // The value of lane K of the quad.
 template <int K, typename V>
@@ -982,49 +973,50 @@ __device__ inline V quad_get(V v) {
         return __builtin_bit_cast(V, lo | (hi << 32));
     }
 }
-__device__ inline bool quad_any(bool v) {
-    uint32_t m = v ? 1u : 0u;
-    m |= quad_perm<0xb1>(m);   // lanes 1 0 3 2
-    m |= quad_perm<0x4e>(m);   // lanes 2 3 0 1
-    return m != 0u;
-}
-
 // acc -= sum_c val[e][r][c] * x[3 col[e] + c] over the blocks [lo, hi) of a
-// row, ascending, once the entries of x are there.
-template <bool XCD, typename T, typename TX>
-__device__ inline T flow_walk(const int32_t *__restrict__ col, const T *__restrict__ val, int lo, int hi, int r,
-                              const FlowSrc<TX, XCD> &x, T acc, SweepCtr *ctr, int spin) {
+// row, ascending, once the entries of x are there.  The wave's rows wait
+// together (they meet again behind the loop anyway), so the loop and its
+// exit are scalar; NB blocks a pass, absent ones zero (acc - 0 keeps acc),
+// so that no branch separates the products.
+template <int NB, typename T, typename TX>
+__device__ inline T flow_pass(const int32_t *__restrict__ col, const T *__restrict__ val, int e, int hi, int r,
+                              const TX *x, T acc, SweepCtr *ctr, int spin) {
     using Bits = typename FlowBits<TX>::type;
-    constexpr int NB = 4;
-    for (int e = lo; e < hi; e += NB) {
-        int j[NB];
-        T b[NB][3];
-        Bits xv[NB];
+    int j[NB];
+    T b[NB][3];
+    Bits xv[NB];
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int ee = min(e + u, hi - 1);
-            j[u] = col[ee];
-            const T *bp = val + (size_t)ee * 9 + 3 * r;
+    for (int u = 0; u < NB; ++u) {
+        j[u] = -1;
+        b[u][0] = b[u][1] = b[u][2] = 0;
+        if (e + u < hi) {
+            j[u] = 3 * col[e + u] + r;
+            const T *bp = val + (size_t)(e + u) * 9 + 3 * r;
             b[u][0] = bp[0]; b[u][1] = bp[1]; b[u][2] = bp[2];
         }
-        int spins = 0;
-        for (;;) {
-            bool miss = false;
-#pragma unroll
-            for (int u = 0; u < NB; ++u)
-                if (e + u < hi) xv[u] = x.load(3 * j[u] + r);
-#pragma unroll
-            for (int u = 0; u < NB; ++u)
-                if (e + u < hi) miss |= xv[u] == FlowBits<TX>::mark;
-            if (!quad_any(miss) || flow_give_up(ctr, spins, spin)) break;
-        }
-#pragma unroll
-        for (int u = 0; u < NB; ++u)
-            if (e + u < hi) {
-                const T v = (T)__builtin_bit_cast(TX, xv[u]);
-                acc -= dot3(b[u][0], b[u][1], b[u][2], quad_get<0>(v), quad_get<1>(v), quad_get<2>(v));
-            }
     }
+    int spins = 0;
+    for (;;) {
+        bool miss = false;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) xv[u] = flow_load(x + max(j[u], 0));
+#pragma unroll
+        for (int u = 0; u < NB; ++u) miss |= (j[u] >= 0) & (xv[u] == FlowBits<TX>::mark);
+        if (!__any(miss) || flow_give_up(ctr, spins, spin)) break;
+        asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        const T v = j[u] >= 0 ? (T)__builtin_bit_cast(TX, xv[u]) : (T)0;
+        acc -= dot3(b[u][0], b[u][1], b[u][2], quad_get<0>(v), quad_get<1>(v), quad_get<2>(v));
+    }
+    return acc;
+}
+template <typename T, typename TX>
+__device__ inline T flow_walk(const int32_t *__restrict__ col, const T *__restrict__ val, int lo, int hi, int r,
+                              const TX *x, T acc, SweepCtr *ctr, int spin) {
+    if (!__any(hi - lo > 3)) return flow_pass<3>(col, val, lo, hi, r, x, acc, ctr, spin);
+    for (int e = lo; __any(e < hi); e += 4) acc = flow_pass<4>(col, val, e, hi, r, x, acc, ctr, spin);
     return acc;
 }
 
@@ -1056,8 +1048,7 @@ __global__ void __launch_bounds__(kRowThreads) k_lsweep_flow(DevSchedule d, cons
             acc = (T)in[k];
         }
         if (fl.own) flow_mark(z + k);
-        const FlowSrc<T, XCD> src(y + vo, vstride);
-        acc = flow_walk<XCD>(d.lcol, L + (size_t)sys * l_stride, d.lptr[fl.q], d.lptr[fl.q + 1], fl.r, src, acc, ctr,
+        acc = flow_walk(d.lcol, L + (size_t)sys * l_stride, d.lptr[fl.q], d.lptr[fl.q + 1], fl.r, (const T *)y + vo, acc, ctr,
                              spin);
         if (fl.own) flow_store<XCD>(y + k, acc);
     });
@@ -1083,11 +1074,320 @@ __global__ void __launch_bounds__(kRowThreads) k_usweep_flow(DevSchedule d, cons
         if (fl.own) flow_mark(y + k);
         const T *dp = Dinv + (size_t)sys * d_stride + (size_t)fl.q * 9 + 3 * fl.r;
         const T d0 = dp[0], d1 = dp[1], d2 = dp[2];
-        const FlowSrc<double, XCD> src(z + vo, vstride);
-        acc = flow_walk<XCD>(d.ucol, U + (size_t)sys * u_stride, d.uptr[fl.q], d.uptr[fl.q + 1], fl.r, src, acc, ctr,
+        acc = flow_walk(d.ucol, U + (size_t)sys * u_stride, d.uptr[fl.q], d.uptr[fl.q + 1], fl.r, (const double *)z + vo, acc, ctr,
                              spin);
         const double zr = (double)dot3(d0, d1, d2, quad_get<0>(acc), quad_get<1>(acc), quad_get<2>(acc));
         if (fl.own) flow_store<XCD>(z + k, zr);
+    });
+}
+
+// --------------------------------------------- single-launch factorisation
+
+// Before a single-launch factorisation: the reordered copy A' of every
+// block, inv(U_ii) marked everywhere, the pivot record and the launch's
+// counter cleared.  Consecutive threads move consecutive elements.
+__global__ void __launch_bounds__(kRowThreads) k_factor_flow_prep(DevSchedule d, const double *__restrict__ A,
+                                                                  size_t a_stride, double *__restrict__ Ap,
+                                                                  double *__restrict__ Dinv,
+                                                                  int32_t *__restrict__ bad, SweepCtr *ctr) {
+    const int sys = blockIdx.y;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        bad[sys] = kNoBadRow;
+        if (sys == 0) ctr->owner = ctr->ticket = ctr->error = 0u;
+    }
+    const double *As = A + (size_t)sys * a_stride;
+    double *Aps = Ap + (size_t)sys * d.nnzb * 9, *Ds = Dinv + (size_t)sys * d.n * 9;
+    const size_t total = (size_t)d.nnzb * 9, nd = (size_t)d.n * 9;
+    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
+        const size_t p = t / 9;
+        Aps[t] = As[(size_t)d.psrc[p] * 9 + (t - 9 * p)];
+        if (t < nd) flow_mark(Ds + t);
+    }
+}
+
+// out = row (a0 a1 a2) times the 3x3 block whose row r lane r of the quad
+// holds in m (row3_mul's operations and order).
+__device__ inline void quad_mul(const double (&a)[3], const double (&m)[3], double (&out)[3]) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        out[c] = __builtin_fma(a[2], quad_get<2>(m[c]), __builtin_fma(a[1], quad_get<1>(m[c]), a[0] * quad_get<0>(m[c])));
+}
+
+// All levels of the factorisation in one launch: k_factor_level's row
+// arithmetic, a quad per block row, each row waiting for inv(U_kk) of its
+// lower neighbours (marked by the launch before).  The blocks an update
+// needs are A' blocks wherever nothing updates them (the update list names
+// them so), present before the launch; a U block that is updated is stored
+// before its row's inv(U_kk), and read after it.  Bound by the dependency
+// chain, 1.6-1.9 us a level on one XCD: one store and one load, two block
+// products and a 3x3 inverse.  63 levels (10 000-cell grid) take 115 us, 697
+// with a launch a level; 1 791 levels (96k cells with NNCs) 2.8 ms, 22.1.
+template <bool F32, int FM, bool XCD>
+__global__ void __launch_bounds__(kRowThreads) k_factor_flow(DevSchedule d, const double *__restrict__ Ap,
+                                                             double *__restrict__ L, double *U,
+                                                             double *Dinv, float *__restrict__ Lf,
+                                                             float *__restrict__ Uf, float *__restrict__ Df,
+                                                             int32_t *__restrict__ bad, int skip_u0, SweepCtr *ctr,
+                                                             int nsys, int spin) {
+    if (!flow_join<XCD>(ctr)) return;
+    flow_items(ctr, d.nlt * nsys, nsys, [&](int tile, int sys) {
+        const FlowLane fl = flow_lane(d.lt_start[tile]);
+        const int q = fl.q, r = fl.r;
+        if (q >= d.lt_start[tile + 1]) return;
+        const double *Aps = Ap + (size_t)sys * d.nnzb * 9;
+        double *Ls = L + (size_t)sys * d.nL * 9;
+        double *Us = U + (size_t)sys * d.nU * 9;
+        double *Ds = Dinv + (size_t)sys * d.n * 9;
+        const int uq = d.l2u[q];
+        const int e0 = d.lptr[q], e1 = d.lptr[q + 1], f0 = d.uptr[uq], f1 = d.uptr[uq + 1];
+        double dr[3];
+        row3_load(Aps + (size_t)d.dsrc[uq] * 9 + 3 * r, dr);
+        bool touched = false;   // a U block of this row was updated
+        bool up = false;
+        int spins = 0;
+        // row r of a U block an update needs
+        auto u_row = [&](int fs, double (&m)[3]) {
+            if (fs < 0) {
+                row3_load(Aps + (size_t)~fs * 9 + 3 * r, m);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) m[c] = __builtin_bit_cast(double, flow_load(Us + (size_t)fs * 9 + 3 * r + c));
+            }
+        };
+        auto u_store = [&](int f, const double (&v)[3]) {
+            if (!fl.own) return;
+            double *t = Us + (size_t)f * 9 + 3 * r;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) flow_store<XCD>(t + c, v[c]);
+        };
+        // inv(U_ii) to the rows that wait for it, and the pivot test
+        auto pivot = [&]() {
+            double a[9], inv[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                a[c] = quad_get<0>(dr[c]);
+                a[3 + c] = quad_get<1>(dr[c]);
+                a[6 + c] = quad_get<2>(dr[c]);
+            }
+            const double det = inv3_row(a, r, inv);
+            if (fl.own) {
+                double *t = Ds + (size_t)uq * 9 + 3 * r;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) flow_store<XCD>(t + c, inv[c]);
+                if (F32) row3_store(Df + ((size_t)sys * d.n + uq) * 9 + 3 * r, inv);
+            }
+            if (up) atomicMin(bad + sys, kBadWait);
+            if (fl.own && r == 0 && (det == 0.0 || !finite(det))) atomicMin(bad + sys, d.lrows[q]);
+        };
+        const bool keep_u = F32 ? false : (e1 > e0 || !skip_u0);
+        const bool keep_uf = F32 && (e1 > e0 || !skip_u0);
+        if (e1 - e0 <= FM && f1 - f0 <= FM) {
+            double lv[FM][3], uv[FM][3], up0[FM][3];
+            uint64_t dv[FM][3];
+            int dq[FM], code0[FM], src0[FM], un[FM], u0[FM];
+            // simple: every lower block updates the row's diagonal only, from
+            // a block of A' (a grid's rows)
+            bool simple = true;
+#pragma unroll
+            for (int t = 0; t < FM; ++t) {
+                u0[t] = un[t] = 0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    lv[t][c] = up0[t][c] = 0.0;
+                    dv[t][c] = 0u;
+                }
+                if (e0 + t < e1) {
+                    row3_load(Aps + (size_t)d.lsrc[e0 + t] * 9 + 3 * r, lv[t]);
+                    dq[t] = d.ldq[e0 + t];
+                    u0[t] = d.upd_ptr[e0 + t];
+                    un[t] = d.upd_ptr[e0 + t + 1];
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < FM; ++t)
+                if (f0 + t < f1) row3_load(Aps + (size_t)d.usrc[f0 + t] * 9 + 3 * r, uv[t]);
+            // the first update of each lower block (on a grid its only one)
+            // is fetched before the wait
+#pragma unroll
+            for (int t = 0; t < FM; ++t)
+                if (u0[t] < un[t]) {
+                    code0[t] = d.upd[2 * u0[t]];
+                    src0[t] = d.upd[2 * u0[t] + 1];
+                    if (src0[t] < 0) row3_load(Aps + (size_t)~src0[t] * 9 + 3 * r, up0[t]);
+                    simple = simple && un[t] - u0[t] == 1 && (code0[t] & 3) == 1 && src0[t] < 0;
+                }
+            for (;;) {
+                bool miss = false;
+#pragma unroll
+                for (int t = 0; t < FM; ++t)
+                    if (e0 + t < e1)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) dv[t][c] = flow_load(Ds + (size_t)dq[t] * 9 + 3 * r + c);
+#pragma unroll
+                for (int t = 0; t < FM; ++t)
+                    if (e0 + t < e1)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) miss |= dv[t][c] == FlowBits<double>::mark;
+                if (!__any(miss)) break;
+                up = flow_give_up(ctr, spins, spin);
+                if (up) break;
+                asm volatile("" ::: "memory");
+            }
+            if (simple) {
+                // no branch between the blocks, so their products overlap;
+                // absent blocks are zero (dr - 0 keeps dr)
+                auto products = [&](auto NTc) {
+                    constexpr int NT = decltype(NTc)::value;
+                    double l[NT][3], pr[NT][3];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        double m[3];
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) m[c] = __builtin_bit_cast(double, dv[t][c]);
+                        quad_mul(lv[t], m, l[t]);
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) quad_mul(l[t], up0[t], pr[t]);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            lv[t][c] = l[t][c];
+                            dr[c] -= pr[t][c];
+                        }
+                };
+                if (__any(e1 - e0 > 3)) products(std::integral_constant<int, FM>{});
+                else products(std::integral_constant<int, 3>{});
+            } else {
+#pragma unroll
+                for (int t = 0; t < FM; ++t) {
+                    if (e0 + t >= e1) continue;
+                    double l[3], m[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) m[c] = __builtin_bit_cast(double, dv[t][c]);
+                    quad_mul(lv[t], m, l);
+                    lv[t][0] = l[0]; lv[t][1] = l[1]; lv[t][2] = l[2];
+                    for (int u = u0[t]; u < un[t]; ++u) {
+                        int code = code0[t];
+                        if (u == u0[t] && src0[t] < 0) {
+                            m[0] = up0[t][0]; m[1] = up0[t][1]; m[2] = up0[t][2];
+                        } else {
+                            code = d.upd[2 * u];
+                            u_row(d.upd[2 * u + 1], m);
+                        }
+                        double pr[3];
+                        quad_mul(l, m, pr);
+                        const int kind = code & 3, pos = code >> 2;
+                        if (kind == 1) {
+                            dr[0] -= pr[0]; dr[1] -= pr[1]; dr[2] -= pr[2];
+                        } else if (kind == 0) {
+#pragma unroll
+                            for (int j = 0; j < FM; ++j)
+                                if (j == pos - e0) { lv[j][0] -= pr[0]; lv[j][1] -= pr[1]; lv[j][2] -= pr[2]; }
+                        } else {
+                            touched = true;
+#pragma unroll
+                            for (int j = 0; j < FM; ++j)
+                                if (j == pos - f0) { uv[j][0] -= pr[0]; uv[j][1] -= pr[1]; uv[j][2] -= pr[2]; }
+                        }
+                    }
+                }
+            }
+            // the pivot's inverse, which other rows wait for, goes out before
+            // the row's own blocks unless one of those is waited for too
+            const bool first = !__any(touched);
+            if (first) pivot();
+#pragma unroll
+            for (int t = 0; t < FM; ++t)
+                if (f0 + t < f1) {
+                    if (keep_u || touched) u_store(f0 + t, uv[t]);
+                    if (keep_uf && fl.own) row3_store(Uf + ((size_t)sys * d.nU + f0 + t) * 9 + 3 * r, uv[t]);
+                }
+#pragma unroll
+            for (int t = 0; t < FM; ++t)
+                if (e0 + t < e1 && fl.own) {
+                    if (F32) row3_store(Lf + ((size_t)sys * d.nL + e0 + t) * 9 + 3 * r, lv[t]);
+                    else row3_store(Ls + (size_t)(e0 + t) * 9 + 3 * r, lv[t]);
+                }
+            if (first) return;
+        } else {
+            // long rows: the same steps on the row's blocks in global memory
+            // (each lane touches its own row of every block)
+            for (int f = f0; f < f1; ++f) {
+                double a[3];
+                row3_load(Aps + (size_t)d.usrc[f] * 9 + 3 * r, a);
+                u_store(f, a);
+            }
+            for (int e = e0; e < e1; ++e) {
+                double a[3];
+                row3_load(Aps + (size_t)d.lsrc[e] * 9 + 3 * r, a);
+                if (fl.own) row3_store(Ls + (size_t)e * 9 + 3 * r, a);
+            }
+            for (int e = e0; e < e1; ++e) {
+                uint64_t dv[3];
+                const int dq = d.ldq[e];
+                for (;;) {
+                    bool miss = false;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        dv[c] = flow_load(Ds + (size_t)dq * 9 + 3 * r + c);
+                        miss |= dv[c] == FlowBits<double>::mark;
+                    }
+                    if (!__any(miss)) break;
+                    up = up || flow_give_up(ctr, spins, spin);
+                    if (up) break;
+                    asm volatile("" ::: "memory");
+                }
+                // lane 3 repeats lane 2's row, whose values lane 2 stores:
+                // it takes every value it reads back from lane 2
+                double a[3], l[3], m[3];
+                row3_load(Ls + (size_t)e * 9 + 3 * r, a);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) m[c] = __builtin_bit_cast(double, dv[c]);
+                quad_mul(a, m, l);
+                if (fl.own) row3_store(Ls + (size_t)e * 9 + 3 * r, l);
+                for (int u = d.upd_ptr[e]; u < d.upd_ptr[e + 1]; ++u) {
+                    const int code = d.upd[2 * u];
+                    double pr[3];
+                    u_row(d.upd[2 * u + 1], m);
+                    quad_mul(l, m, pr);
+                    const int kind = code & 3, pos = code >> 2;
+                    if (kind == 1) {
+                        dr[0] -= pr[0]; dr[1] -= pr[1]; dr[2] -= pr[2];
+                    } else if (fl.own) {
+                        if (kind != 0) touched = true;
+                        double *t = (kind == 0 ? Ls : Us) + (size_t)pos * 9 + 3 * r;
+                        t[0] -= pr[0]; t[1] -= pr[1]; t[2] -= pr[2];
+                    }
+                }
+            }
+            if (F32 && fl.own) {
+                for (int e = e0; e < e1; ++e) {
+                    double a[3];
+                    row3_load(Ls + (size_t)e * 9 + 3 * r, a);
+                    row3_store(Lf + ((size_t)sys * d.nL + e) * 9 + 3 * r, a);
+                }
+                for (int f = f0; f < f1; ++f) {
+                    double a[3];
+                    row3_load(Us + (size_t)f * 9 + 3 * r, a);
+                    row3_store(Uf + ((size_t)sys * d.nU + f) * 9 + 3 * r, a);
+                }
+            }
+            // the finished U where the rows that read it look for it
+            if (touched)
+                for (int f = f0; f < f1; ++f) {
+                    double a[3];
+                    row3_load(Us + (size_t)f * 9 + 3 * r, a);
+                    u_store(f, a);
+                }
+        }
+        // a U block other rows read is in place before inv(U_ii) appears
+        if (__any(touched)) {
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0);
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        }
+        pivot();
     });
 }
 
@@ -2185,12 +2485,12 @@ template void launch_usweep<float>(const DevSchedule &, const float *, size_t, c
 // while the rows of a level (of all systems) are few: an application on 158
 // rows a level (10 000-cell grid) takes 127 us on one XCD and 161 us on all,
 // on 54 rows a level (96k cells with NNCs) 2 460 against 3 840, on 3 400 a
-// level (Block-Jacobi, 113k cells) 273 against 130 (with its permutations).
-// count: entries of the longest vector polled (the XCD's loads address at
-// most 2 GiB of it).
+// level (Block-Jacobi, 113k cells) 273 against 130 (with its permutations;
+// before the waits of a wave became one scalar loop, which took 15-600 us
+// off the shorter time of each).
 constexpr int kFlowXcdRows = 1000;
-static bool flow_one_xcd(int n, int levels, int nsys, size_t count) {
-    return (double)n * nsys <= (double)kFlowXcdRows * levels && count * sizeof(double) < ((size_t)1 << 31);
+static bool flow_one_xcd(int n, int levels, int nsys) {
+    return (double)n * nsys <= (double)kFlowXcdRows * levels;
 }
 // Workgroups of a flow launch: one a CU.  More only add polls of rows far
 // from the front (Block-Jacobi application 130 us at 256, 140 at 512, 170 at
@@ -2207,7 +2507,7 @@ void launch_lsweep_flow(const DevSchedule &d, const T *L, size_t l_stride, const
                         SweepCtr *ctr, SweepCtr *next, int nsys, int levels, int grid, int spin, hipStream_t s,
                         hipEvent_t ev0, hipEvent_t ev1) {
     if (d.nlt <= 0 || nsys <= 0) return;
-    const bool one = flow_one_xcd(d.n, levels, nsys, vstride);
+    const bool one = flow_one_xcd(d.n, levels, nsys);
     const dim3 g(flow_grid(one, grid, d.nlt * nsys));
     auto go = [&](auto kern) {
         launch_ev(kern, g, dim3(kRowThreads), s, ev0, ev1, d, L, l_stride, in, y, z, vstride, r, v, p, st, ctr, next,
@@ -2225,7 +2525,7 @@ void launch_usweep_flow(const DevSchedule &d, const T *U, size_t u_stride, const
                         double *z, size_t vstride, SysState *st, SweepCtr *ctr, SweepCtr *next, int nsys, int levels,
                         int grid, int spin, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     if (d.nut <= 0 || nsys <= 0) return;
-    const bool one = flow_one_xcd(d.n, levels, nsys, vstride);
+    const bool one = flow_one_xcd(d.n, levels, nsys);
     const dim3 g(flow_grid(one, grid, d.nut * nsys));
     auto go = [&](auto kern) {
         launch_ev(kern, g, dim3(kRowThreads), s, ev0, ev1, d, U, u_stride, Dinv, d_stride, y, z, vstride, st, ctr,
@@ -2248,6 +2548,27 @@ template void launch_usweep_flow<double>(const DevSchedule &, const double *, si
 template void launch_usweep_flow<float>(const DevSchedule &, const float *, size_t, const float *, size_t, float *,
                                         double *, size_t, SysState *, SweepCtr *, SweepCtr *, int, int, int, int,
                                         hipStream_t, hipEvent_t, hipEvent_t);
+void launch_factor_flow(const DevSchedule &d, const double *A, size_t a_stride, double *Ap, double *L, double *U,
+                        double *Dinv, float *Lf, float *Uf, float *Df, int32_t *bad, bool skip_u0, bool narrow,
+                        int levels, SweepCtr *ctr, int nsys, hipStream_t s) {
+    if (d.nlt <= 0 || nsys <= 0) return;
+    k_factor_flow_prep<<<dim3(copy_blocks((size_t)d.nnzb * 9), nsys), kRowThreads, 0, s>>>(d, A, a_stride, Ap, Dinv,
+                                                                                          bad, ctr);
+    const bool one = flow_one_xcd(d.n, levels, nsys);
+    const dim3 g(flow_grid(one, kFlowGrid, d.nlt * nsys));
+    auto go = [&](auto F32, auto FM, auto ONE) {
+        k_factor_flow<decltype(F32)::value, decltype(FM)::value, decltype(ONE)::value><<<g, kRowThreads, 0, s>>>(
+            d, Ap, L, U, Dinv, Lf, Uf, Df, bad, skip_u0 ? 1 : 0, ctr, nsys, kSpinLimitDefault);
+    };
+    auto scope = [&](auto F32, auto FM) {
+        if (one) go(F32, FM, std::true_type{}); else go(F32, FM, std::false_type{});
+    };
+    auto width = [&](auto F32) {
+        if (narrow) scope(F32, std::integral_constant<int, kFactorNarrow>{});
+        else scope(F32, std::integral_constant<int, kFactorWide>{});
+    };
+    if (Lf) width(std::true_type{}); else width(std::false_type{});
+}
 void launch_flow_mark(void *p, size_t bytes, hipStream_t s) {
     launch_fill_u32((uint32_t *)p, bytes / sizeof(uint32_t), kMark, s);
 }

@@ -7,10 +7,17 @@ and inputs that hold NaN, the mark's own bit pattern among them."""
 import numpy as np
 import pytest
 
+import oracle
 import paper_2309_11488_amd as rs
 from synth import make_ensemble, make_grid_system
 
 pytestmark = pytest.mark.gpu
+
+
+
+def rel_block_err(a, b):
+    return np.abs(a - b).max(initial=0.0) / max(np.abs(b).max(initial=0.0), 1e-300)
+
 
 MARK = np.array([0x7FF4BEEF7FF4BEEF], np.uint64).view(np.float64)[0]
 
@@ -67,3 +74,50 @@ def test_single_launch_sweeps_equal_per_level(name, ordering, precision):
             for _ in range(2):
                 got = rs.ilu0_apply(s.M, v, n_sys=batch)
                 assert np.array_equal(got, want, equal_nan=True)
+
+
+@pytest.mark.parametrize("precision", [rs.PREC_FP64, rs.PREC_FP32_FACTORS])
+@pytest.mark.parametrize("name", ["chain_3", "chain_70", "dense_9", "dense_40", "grid16x8x8", "grid40x17x11", "nnc",
+                                  "ensemble", "wide_ensemble"])
+def test_single_launch_factorisation_equals_the_oracle(name, precision):
+    """Factors of patterns whose factorisation is one launch (more than two
+    levels), short rows and rows past the register width, with and without
+    updates of U blocks, on one XCD and on all (an ensemble wide enough):
+    the oracle's under the same ordering, and again after a refactorisation
+    with other values."""
+    if name == "wide_ensemble":
+        s = make_ensemble(40, 17, 11, seeds=list(range(24)))
+        rowptr, colidx, vals = s.rowptr, s.colidx, s.vals
+    else:
+        rowptr, colidx, vals = _pattern(name)
+    n, nnzb = len(rowptr) - 1, len(colidx)
+    with rs.Solver(rowptr, colidx, vals[::-1].copy() * 2.0, ordering=rs.ORDER_LEVEL_SET, precision=precision) as s:
+        s.factor()
+        st, bad = s.factor(vals)
+        assert st == rs.OK and (bad == -1).all()
+        for k in (0, vals.shape[0] - 1):
+            lu, dinv = rs.ilu0_get_factors(s.M, k, n, nnzb)
+            perm, _, _ = rs.ilu0_get_schedule(s.M, n)
+            prow, pcol, pv = oracle.permute(rowptr, colidx, vals[k], perm)
+            st, _, olu, odinv = oracle.ilu0(prow, pcol, pv)
+            assert st == oracle.OK
+            offd = pcol != np.repeat(np.arange(n), np.diff(prow))
+            for got, want in ((lu[offd], olu[offd]), (dinv, odinv)):
+                if precision == rs.PREC_FP64:
+                    assert rel_block_err(got, want) <= 1e-12
+                else:
+                    w32 = want.astype(np.float32)
+                    assert np.all(np.abs(got - w32.astype(np.float64)) <= np.spacing(np.abs(w32)).astype(np.float64))
+
+
+def test_single_launch_factorisation_reports_a_zero_pivot():
+    rowptr, colidx, vals = _pattern("grid16x8x8")
+    vals = vals.copy()
+    row = 700
+    for p in range(rowptr[row], rowptr[row + 1]):
+        vals[0, p, 1] = 0.0
+    with rs.Solver(rowptr, colidx, vals, ordering=rs.ORDER_LEVEL_SET) as s:
+        st, bad = s.factor()
+        assert st == rs.ZERO_PIVOT and bad[0] == row
+        st, bad = s.factor(_pattern("grid16x8x8")[2])
+        assert st == rs.OK and bad[0] == -1
