@@ -135,6 +135,8 @@ enum rs_option {
                                 With separate wells (bcsr_set_wells), the well terms of those
                                 rows, which need the whole product's x, are subtracted after
                                 the SpMV by a small launch that also corrects the dot products.
+                                Systems of few rows (and no wells) run a whole application and
+                                its SpMV as one launch, whatever the pattern, with the same bits.
                                 Used with per-level sweeps and reduction split 0; 0: never */
     RS_OPT_FUSED_ROWS = 10,  /* read only (ilu0_get_option): how many rows the analysed pattern
                                 lets RS_OPT_FUSE_SPMV fuse (0: none) */

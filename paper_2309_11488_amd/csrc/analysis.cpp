@@ -331,17 +331,22 @@ int make_ordering(int n, const int32_t *rowptr, const int32_t *colidx, int order
     return make_ordering(n, rowptr, colidx, ordering, perm, sp);
 }
 
-// Split every level into tiles of at most R rows: the tiles' first schedule
-// positions, then n.
-static void make_tiles(int n, int nlev, const std::vector<int32_t> &lev_ptr, int R, std::vector<int32_t> &start) {
+// Split the levels from lev0 on into tiles of at most R rows: the tiles' first
+// schedule positions, then n.  A tile starts at position `cut` too (the end
+// of the fused rows, or 0).
+static void make_tiles(int n, int lev0, int nlev, const std::vector<int32_t> &lev_ptr, int R, int cut,
+                       std::vector<int32_t> &start) {
     start.clear();
-    for (int l = 0; l < nlev; ++l)
-        for (int q = lev_ptr[l]; q < lev_ptr[l + 1]; q += R) start.push_back(q);
+    for (int l = lev0; l < nlev; ++l)
+        for (int q = lev_ptr[l]; q < lev_ptr[l + 1];) {
+            start.push_back(q);
+            q = q < cut && q + R > cut ? cut : q + R;
+        }
     start.push_back(n);
 }
 
 int build_schedule(int n, int nnzb, const int32_t *rowptr, const int32_t *colidx, int ordering, Schedule &s,
-                   int tile_rows, const int32_t *part) {
+                   int tile_rows, int large_rows, int small_rows, const int32_t *part) {
     s = Schedule();
     s.n = n;
     s.nnzb = nnzb;
@@ -552,8 +557,19 @@ int build_schedule(int n, int nnzb, const int32_t *rowptr, const int32_t *colidx
                 s.lconsec[l] = 0;
                 break;
             }
-    make_tiles(n, s.nl_levels, s.lset, tile_rows, s.ltiles);
-    make_tiles(n, s.nu_levels, s.uset, tile_rows, s.utiles);
+    make_tiles(n, 0, s.nl_levels, s.lset, tile_rows, 0, s.ltiles);
+    make_tiles(n, 0, s.nu_levels, s.uset, tile_rows, 0, s.utiles);
+    auto apply_tiles = [&](int R, Schedule::ApplyTiles &t) {
+        const int cut = s.fuse_n0 > 0 ? s.fuse_q0 + s.fuse_n0 : 0;
+        make_tiles(n, 0, s.nl_levels, s.lset, R, 0, t.lt);
+        make_tiles(n, 1, s.nu_levels, s.uset, R, cut, t.ut);
+        if (s.fuse_n0 > 0) {
+            t.uf0 = (int)(std::find(t.ut.begin(), t.ut.end(), s.fuse_q0) - t.ut.begin());
+            t.nf = (s.fuse_n0 + R - 1) / R;
+        }
+    };
+    apply_tiles(large_rows, s.tiles_large);
+    apply_tiles(small_rows, s.tiles_small);
     return RS_OK;
 }
 

@@ -83,12 +83,20 @@ struct Schedule {
     // row tiles of the single-launch sweeps: tile t covers schedule
     // positions [ltiles[t], ltiles[t+1]) inside one level
     std::vector<int32_t> ltiles, utiles;
+    // tiles of the single-launch application, inside one level (first rows,
+    // then the end), the upper ones from the second upper level on; upper
+    // tiles [uf0, uf0 + nf) hold the fuse_n0 rows, in order from the first
+    struct ApplyTiles {
+        std::vector<int32_t> lt, ut;
+        int uf0 = 0, nf = 0;
+    } tiles_large, tiles_small;
 };
 
-// tile_rows: rows per sweep tile (a multiple of the rows one workgroup covers).
+// tile_rows: rows per tile of a single-launch sweep; large_rows, small_rows:
+// of the two tile sizes of a single-launch application.
 // part: optional partition id per row (Block-Jacobi-ILU0), else plain ILU0.
 int build_schedule(int n, int nnzb, const int32_t *rowptr, const int32_t *colidx, int ordering, Schedule &s,
-                   int tile_rows, const int32_t *part = nullptr);
+                   int tile_rows, int large_rows, int small_rows, const int32_t *part = nullptr);
 
 // Grow n_parts partitions of near-equal size (sizes differ by at most one):
 // each starts from the first unassigned row in natural order and repeatedly

@@ -222,7 +222,7 @@ struct Analysis {
     DevSchedule dev{};
     DevBuf perm, prow, pcol, psrc, lrows, lptr, lcol, lsrc, ldq, l2u, upd_ptr, upd, urows, uptr, ucol, usrc, dsrc;
     DevBuf lsrc_a, usrc_a, dsrc_a, rest_dst, rest_src;
-    DevBuf lt_start, ut_start;
+    DevBuf lt_start, ut_start, la_start, ua_start, ls_start, us_start;
     // U blocks of rows with lower blocks: with FP32 factors the only U the
     // factorisation keeps in FP64 (later levels' updates read it)
     double u_kept = 0;
@@ -238,7 +238,7 @@ struct rs_ilu0 {
     DevBuf pvals, L, U, Dinv, Lf, Uf, Dinvf, bad;
     std::vector<int32_t> bad_host;
     // solve workspace
-    DevBuf work, ywork, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
+    DevBuf work, ywork, ywork2, ftickets, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
     bool y_marked = false;     // ywork holds the mark everywhere (single-launch sweeps)
     Krylov k{};
     // GMRES workspace: Krylov basis, per-system cycle state, reduction partials
@@ -290,12 +290,13 @@ struct rs_ilu0 {
     // every setting a captured iteration depends on
     struct GraphKey {
         int precision = -1, tile_sweeps = 0, spmv_variant = 0, sweep_variant = 0, split = 0, sweep_grid = 0;
-        int spin = 0, fuse = 0, yin = 0, lp = 0;
+        int spin = 0, fuse = 0, yin = 0, lp = 0, flow = 0;
         long long wells = 0;   // 0: no wells, else the wells' version + 1
         bool operator==(const GraphKey &o) const {
             return precision == o.precision && tile_sweeps == o.tile_sweeps && spmv_variant == o.spmv_variant &&
                    sweep_variant == o.sweep_variant && split == o.split && sweep_grid == o.sweep_grid &&
-                   spin == o.spin && fuse == o.fuse && yin == o.yin && lp == o.lp && wells == o.wells;
+                   spin == o.spin && fuse == o.fuse && yin == o.yin && lp == o.lp && flow == o.flow &&
+                   wells == o.wells;
         }
     };
     struct Segment {
@@ -547,7 +548,7 @@ static int build_analysis(const rs_bcsr *A, int32_t ordering, const int32_t *par
     auto an = std::make_shared<Analysis>();
     an->hash = A->hash;
     rs::build_schedule(A->n, A->nnzb, A->h_rowptr.data(), A->h_colidx.data(), ordering, an->sch, rs::kFlowRows,
-                       part);
+                       rs::kApplyRows, rs::kApplyRowsSmall, part);
     const rs::Schedule &S = an->sch;
     for (int q = 0; q < S.n; ++q)
         if (S.lptr[q + 1] > S.lptr[q]) an->u_kept += S.uptr[S.l2u[q] + 1] - S.uptr[S.l2u[q]];
@@ -559,7 +560,8 @@ static int build_analysis(const rs_bcsr *A, int32_t ordering, const int32_t *par
         {&an->urows, &S.urows}, {&an->uptr, &S.uptr}, {&an->ucol, &S.ucol}, {&an->usrc, &S.usrc},
         {&an->dsrc, &S.dsrc}, {&an->lsrc_a, &S.lsrc_a}, {&an->usrc_a, &S.usrc_a}, {&an->dsrc_a, &S.dsrc_a},
         {&an->rest_dst, &S.rest_dst}, {&an->rest_src, &S.rest_src}, {&an->lt_start, &S.ltiles},
-        {&an->ut_start, &S.utiles}};
+        {&an->ut_start, &S.utiles}, {&an->la_start, &S.tiles_large.lt}, {&an->ua_start, &S.tiles_large.ut},
+        {&an->ls_start, &S.tiles_small.lt}, {&an->us_start, &S.tiles_small.ut}};
     // uploads on a private stream, complete before the handle is returned,
     // so that any stream may use the analysis
     hipStream_t us = nullptr;
@@ -588,6 +590,12 @@ static int build_analysis(const rs_bcsr *A, int32_t ordering, const int32_t *par
     d.fuse_n0 = S.fuse_n0; d.fuse_q0 = S.fuse_q0;
     d.nlt = (int)S.ltiles.size() - 1; d.nut = (int)S.utiles.size() - 1;
     d.lt_start = an->lt_start.as<int32_t>(); d.ut_start = an->ut_start.as<int32_t>();
+    auto tiles = [](const rs::Schedule::ApplyTiles &t, const DevBuf &lt, const DevBuf &ut) {
+        return DevSchedule::ApplyTiles{lt.as<int32_t>(), ut.as<int32_t>(), (int)t.lt.size() - 1, (int)t.ut.size() - 1,
+                                       t.uf0, t.nf};
+    };
+    d.tiles_large = tiles(S.tiles_large, an->la_start, an->ua_start);
+    d.tiles_small = tiles(S.tiles_small, an->ls_start, an->us_start);
     out = std::move(an);
     return RS_OK;
 }
@@ -1020,6 +1028,9 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
     k.s = w + 5 * vec; k.shat = w + 6 * vec; k.t = w + 7 * vec; k.x = w + 8 * vec;
     k.vstride = vs;
     k.y = M->ywork.p;
+    k.y2 = M->ywork2.p;
+    k.ftickets = M->ftickets.as<uint32_t>();
+    k.fticket_stride = rs::ticket_stride_for(rs::fuse_blocks(M->an->sch.fuse_n0, 1));
     k.part = M->part.as<double>();
     k.part_stride = pstride;
     k.tickets = M->tickets.as<uint32_t>();
@@ -1266,8 +1277,87 @@ static int class_parts(int mask) {
     return parts;
 }
 
+// Whether a BiCGStab iteration runs each application and its product as one
+// launch (k_apply_flow, the same bits): systems of few rows (of all systems),
+// whose launches cost more than their bytes, where the launches may be fused
+// at all (RS_OPT_FUSE_SPMV) and no sweep or product is timed on its own.
+// Solves at reduction 1e-2, one launch against separate ones: 96k cells with
+// NNCs, four colours 387 against 436 us, 33 RCM levels 571 against 1 432; four
+// colours and 150k cells 473 against 519, 280k cells no faster.  Two-level
+// patterns have fewer launches to save: 4 000 cells 177 against 214 us, 20 000
+// cells 223 against 233, 50 000 cells 259 against 263 in FP64, 245 against 261
+// with FP32 factors.  Not with RS_OPT_USE_GRAPH off, which says that other
+// threads solve meanwhile: waiting workgroups hold CUs that the others'
+// launches would fill (a burst of 24 requests of 10 000 to 200 000 cells on
+// four slots 4.91 against 4.41 ms).
+constexpr long long kFlowRowsMany = 200000, kFlowRowsTwo = 30000, kFlowRowsTwoF32 = 60000;
+static bool flow_iteration(const rs_ilu0 *M) {
+    const int single = 1 << PC_LSWEEP | 1 << PC_USWEEP | 1 << PC_SPMV_V | 1 << PC_SPMV_T;
+    const long long most = !M->an->sch.y_in ? kFlowRowsMany
+                           : M->precision == RS_PREC_FP64 ? kFlowRowsTwo : kFlowRowsTwoF32;
+    return M->use_graph && M->fuse_spmv && !M->tile_sweeps && M->split() == 0 && M->wdev.nw == 0 && !(g_prof.mask & single) &&
+           (long long)M->n * M->batch <= most;
+}
+// Workgroups of such a launch: as many as fit on the device at once (16
+// waves each, one a CU).
+constexpr int kFlowApplyGrid = 512;
+// The second y and the second reduction counters of such iterations,
+// allocated on first use (and kept).
+static int ensure_flow(ilu0_t M, hipStream_t s) {
+    if (M->ftickets.p) return RS_OK;
+    const size_t tb = (size_t)M->batch * M->k.fticket_stride * sizeof(uint32_t);
+    HIP_TRY(M->ywork2.alloc(std::max<size_t>((size_t)M->batch * rs::vec_stride(M->n), 1) * sizeof(double)));
+    HIP_TRY(M->ftickets.alloc(tb));
+    HIP_TRY(hipMemsetAsync(M->ftickets.p, 0, tb, s));
+    M->k.y2 = M->ywork2.p;
+    M->k.ftickets = M->ftickets.as<uint32_t>();
+    return RS_OK;
+}
+
+// One such iteration: the first application marks shat and the second y for
+// the second application, which marks the first y again; the full-step
+// update marks phat.
+template <typename T>
+static void enqueue_flow_iteration(ilu0_t M, const T *L, const T *U, const T *D, hipStream_t s) {
+    Krylov &k = M->k;
+    const int B = M->batch, u0_end = M->an->sch.uset[1];
+    const double n = M->n, nnzb = M->nnzb, tb = sizeof(T);
+    const bool fz = fused_iteration(M);
+    const bool lp = sizeof(T) == sizeof(double) && lower_parts_iteration(M);
+    const double product = B * (76 * nnzb + 52 * n);
+    const double bytes1 = lower_bytes(M, tb, B) + upper_bytes(M, tb, B) + product +
+                          (lp ? lp_upper_extra(M, B) + lp_spmv_extra(M, B) : 0.0);
+    const double bytes2 = (lp ? lp_lower_bytes(M, B) : lower_bytes(M, tb, B)) + upper_bytes(M, tb, B) + product;
+    const double *Ap = M->pvals.as<double>();
+    T *ya = (T *)k.y, *yb = (T *)k.y2;
+    {
+        ProfScope ps(PC_APPLY, s, bytes1, true);
+        rs::launch_apply_flow<T>(M->an->dev, L, U, D, Ap, nullptr, ya, yb, k.phat, k.shat, k.v, k.rhat, k, k.st,
+                                 k.lctr, k.uctr, u0_end, B, rs::APPLY_V, fz, lp, M->spmv_variant, M->an->sch.nl_levels, kFlowApplyGrid,
+                                 M->spin_limit, s, ps.start(), ps.stop());
+    }
+    {
+        ProfScope ps(PC_VEC, s, B * 72 * n, true);
+        rs::launch_s_update(M->an->dev, k, B, M->spmv_variant, 0, fz, s, ps.start(), ps.stop());
+    }
+    {
+        ProfScope ps(PC_APPLY, s, bytes2, true);
+        rs::launch_apply_flow<T>(M->an->dev, L, U, D, Ap, k.s, yb, ya, k.shat, nullptr, k.t, k.s, k, k.st, k.uctr,
+                                 k.lctr, u0_end, B, rs::APPLY_T, fz, lp, M->spmv_variant, M->an->sch.nl_levels, kFlowApplyGrid,
+                                 M->spin_limit, s, ps.start(), ps.stop());
+    }
+    {
+        ProfScope ps(PC_VEC, s, B * 192 * n, true);
+        rs::launch_xr_update(M->an->dev, k, B, M->spmv_variant, 0, fz, s, ps.start(), ps.stop(), false, true);
+    }
+}
+
 template <typename T>
 static void enqueue_iteration(ilu0_t M, const T *L, const T *U, const T *D, hipStream_t s, int parts) {
+    if (parts == P_ALL && flow_iteration(M)) {
+        enqueue_flow_iteration<T>(M, L, U, D, s);
+        return;
+    }
     Krylov &k = M->k;
     const int B = M->batch;
     const size_t per = (size_t)M->nnzb * 9;
@@ -1365,6 +1455,7 @@ static int replay_segment(ilu0_t M, int parts, hipStream_t s, int reps = 1) {
     key.fuse = fused_iteration(M) ? 1 : 0;
     key.yin = M->y_input ? 1 : 0;
     key.lp = M->lower_parts ? 1 : 0;
+    key.flow = parts == P_ALL && flow_iteration(M) ? 1 : 0;
     key.wells = M->wdev.nw > 0 ? (long long)M->wells_version + 1 : 0;
     rs_ilu0::Segment &seg = M->segments[parts + (reps - 1) * kRepShift];
     if (!seg.exec || !(seg.key == key)) {
@@ -1403,6 +1494,12 @@ static int run_iteration(ilu0_t M, hipStream_t s) {
     }
     const int timed = class_parts(g_prof.mask);
     if (!timed) return replay_segment(M, P_ALL, s);
+    if (flow_iteration(M)) {
+        // every launch is a unit of its own: its events come with the dispatch
+        enqueue_iteration_any(M, s, P_ALL);
+        HIP_TRY(hipGetLastError());
+        return RS_OK;
+    }
     const double tb = M->precision == RS_PREC_FP32_FACTORS ? 4 : 8;
     // the SpMV rows a fused upper launch forms count with the application
     const double fb = fused_iteration(M) ? fused_spmv_bytes(M, M->batch) : 0.0;
@@ -1643,7 +1740,12 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
     if (st != RS_OK) return st;
     st = ensure_wells(M, A, s);
     if (st != RS_OK) return st;
-    if (reads_u(M, fused_iteration(M)) && (st = ensure_u(M, s)) != RS_OK) return st;
+    const bool flow = flow_iteration(M);
+    if (flow) {
+        if ((st = ensure_flow(M, s)) != RS_OK) return st;
+    } else if (reads_u(M, fused_iteration(M)) && (st = ensure_u(M, s)) != RS_OK) {
+        return st;
+    }
     if (lower_parts_iteration(M) && (st = ensure_lower_parts(M, s)) != RS_OK) return st;
     const size_t m = 3 * (size_t)M->n * B;
     const double *bd = nullptr;
@@ -1659,7 +1761,7 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
     if (st != RS_OK) return st;
     {
         ProfScope ps(PC_VEC, s, (double)B * 152 * M->n);
-        rs::launch_setup(M->an->dev, bd, M->bad.as<int32_t>(), reduction, max_iter, k, B, s);
+        rs::launch_setup(M->an->dev, bd, M->bad.as<int32_t>(), reduction, max_iter, k, B, flow, s);
     }
     // x back to the caller's order, the true residual, and the results to the host
     auto finish = [&]() -> int {
@@ -1668,8 +1770,8 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipEventRecord(M->ev_s1, s));
         HIP_TRY(hipMemcpyAsync(M->h_state, k.st, B * sizeof(SysState), hipMemcpyDeviceToHost, s));
-        // only single-launch sweeps touch the sweep counters
-        if (M->tile_sweeps) HIP_TRY(hipMemcpyAsync(M->h_ctr, k.lctr, 2 * sizeof(rs::SweepCtr), hipMemcpyDeviceToHost, s));
+        // only single-launch sweeps and applications touch the counters
+        if (M->tile_sweeps || flow) HIP_TRY(hipMemcpyAsync(M->h_ctr, k.lctr, 2 * sizeof(rs::SweepCtr), hipMemcpyDeviceToHost, s));
         if (mem != RS_MEM_DEVICE) HIP_TRY(hipMemcpyAsync(x, xd, m * sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         return RS_OK;
@@ -1710,7 +1812,7 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
         st = finish();
         if (st != RS_OK) return st;
     }
-    if (M->tile_sweeps && (M->h_ctr[0].error || M->h_ctr[1].error)) return sweep_reset(M, s);
+    if ((M->tile_sweeps || flow) && (M->h_ctr[0].error || M->h_ctr[1].error)) return sweep_reset(M, s);
     const double solve_ms = elapsed_ms(M->ev_s0, M->ev_s1);
     int worst = RS_OK, needed = 1;
     for (int i = 0; i < B; ++i) {
@@ -1878,7 +1980,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         // r = rhat = P b, x = 0, ||b||, the initial tests; the first cycle
         // starts from v_0 = r / ||b||
         ProfScope ps(PC_VEC, s, (double)B * 152 * M->n);
-        rs::launch_setup(M->an->dev, bd, M->bad.as<int32_t>(), reduction, max_iter, k, B, s);
+        rs::launch_setup(M->an->dev, bd, M->bad.as<int32_t>(), reduction, max_iter, k, B, false, s);
     }
     rs::launch_gm_init(g, B, s);
     rs::launch_gm_normalise(g, k.r, 0, 0, M->n, B, s);

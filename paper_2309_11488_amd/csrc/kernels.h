@@ -37,6 +37,11 @@ struct DevSchedule {
     // sweep tiles (see Schedule::Tiles)
     int nlt, nut;
     const int32_t *lt_start, *ut_start;
+    // tiles of the single-launch application (Schedule::ApplyTiles)
+    struct ApplyTiles {
+        const int32_t *lt, *ut;
+        int nl, nu, uf0, nf;
+    } tiles_large, tiles_small;
 };
 
 // Standard wells kept separate (y -= C^T D^-1 B x for every well), as the
@@ -86,10 +91,13 @@ struct Krylov {
     double *r, *rhat, *p, *v, *phat, *s, *shat, *t, *x;
     size_t vstride;
     void *y;            // lower-sweep intermediate, FP64 or FP32 (factor type)
+    void *y2;           // a second one (single-launch applications, else NULL)
     double *part;       // reduction partials, nsys * part_stride
     size_t part_stride;
     uint32_t *tickets;  // reduction ticket counters, nsys * ticket_stride
     size_t ticket_stride;
+    uint32_t *ftickets; // counters of the fused upper rows' partials in launch_apply_flow
+    size_t fticket_stride;
     double *spart;      // per-workgroup partials of the two SpMVs, nsys * spart_stride
     size_t spart_stride;
     double *fpart;      // partials of the products formed by the fused upper launch, nsys * fpart_stride
@@ -106,6 +114,9 @@ constexpr int kWavesPerBlock = 4;
 constexpr int kRowsPerBlock = kRowsPerWave * kWavesPerBlock;  // 84 block rows per workgroup
 constexpr int kRowThreads = kWave * kWavesPerBlock;           // 256
 constexpr int kFlowRows = 64;                                 // rows of a tile of the single-launch sweeps
+// rows of a tile of the single-launch application: whole workgroups of the
+// row kernels, for their partials
+constexpr int kApplyRows = 252, kApplyRowsSmall = 84;
 constexpr int kVecThreads = 256;
 constexpr int kVecItems = 4;                                // entries per thread per tile
 constexpr int kVecTile = kVecThreads * kVecItems;           // 1024 entries
@@ -256,8 +267,27 @@ void launch_spmv(int n, const int32_t *ptr, const int32_t *col, const double *A,
 // The two SpMVs store per-workgroup partial sums; the s- and x/r-updates
 // that follow add them (their launch shape fixes the partials' count).
 // bad[sys] < n marks a system whose factorisation hit a singular pivot.
+// flow: also mark y and phat for launch_apply_flow.
 void launch_setup(const DevSchedule &d, const double *b_orig, const int32_t *bad, double reduction, int max_iter,
-                  Krylov &k, int nsys, hipStream_t s);
+                  Krylov &k, int nsys, bool flow, hipStream_t s);
+// One launch for an application z = M^-1 in and the product that follows.
+// On entry y and z hold the mark; y_next and z_next (may be NULL) receive it.
+// APPLY_V: the input is p = r + beta (p - omega v), updated in place, and out
+// = A' z leaves its dot products with w1 and itself where launch_spmv_v (and
+// with fused launch_usweep_spmv) would, for spmv_variant's workgroups;
+// APPLY_T: as launch_spmv_t; APPLY_RUN: out alone; APPLY_ONLY: z alone.
+// fused: the rows [0, d.fuse_n0) of out come with the upper rows; lp: the
+// lower parts (k.lp), formed by APPLY_V and used by APPLY_T.  st may be NULL
+// (all systems).  ctr clear on entry, next is cleared; u0_end: U-schedule
+// positions without upper blocks; levels: of the lower schedule; grid: most
+// workgroups.  The same bits as the separate launches.
+enum ApplyMode { APPLY_ONLY = 0, APPLY_V = 1, APPLY_T = 2, APPLY_RUN = 3 };
+template <typename T>
+void launch_apply_flow(const DevSchedule &d, const T *L, const T *U, const T *Dinv, const double *Ap,
+                       const double *in, T *y, T *y_next, double *z, double *z_next, double *out, const double *w1,
+                       Krylov &k, SysState *st, SweepCtr *ctr, SweepCtr *next, int u0_end, int nsys, int mode,
+                       bool fused, bool lp, int spmv_variant, int levels, int grid, int spin, hipStream_t s,
+                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // t2 = D^-1 (B x) for every well and system (x at stride xstride): the
 // first half of the separate well application, run before an SpMV of x.
 void launch_wells_t2(const WellsDev &w, const double *x, size_t xstride, int nsys, hipStream_t s);
@@ -284,7 +314,8 @@ int wells_fix_at(const DevSchedule &d, int spmv_variant);
 void launch_spmv_t(const DevSchedule &d, const double *Ap, size_t a_stride, Krylov &k, int nsys, int variant, int split,
                    const WellsDev &w, int r0, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_xr_update(const DevSchedule &d, Krylov &k, int nsys, int spmv_variant, int split, bool fused,
-                      hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, bool fix = false);
+                      hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, bool fix = false,
+                      bool flow = false);   // flow: also mark phat for the next iteration's launch_apply_flow
 
 // Which product the fused upper launch forms.
 enum FuseMode { FUSE_NONE = 0, FUSE_V = 1, FUSE_T = 2 };

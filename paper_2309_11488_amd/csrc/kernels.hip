@@ -921,10 +921,10 @@ __device__ inline void flow_clear(SweepCtr *ctr) {
 
 // Run f(tile, system) for the workgroup's items in ticket order.  The last
 // wave draws the tickets (a partly filled tile leaves it idle).
-template <typename F>
+template <int W = kWavesPerBlock, typename F>
 __device__ inline void flow_items(SweepCtr *ctr, int total, int nsys, F &&f) {
     __shared__ int s_item[2];
-    const bool draws = threadIdx.x == kRowThreads - 64;
+    const bool draws = threadIdx.x == 64 * W - 64;
     auto draw = [&]() {
         return (int)__hip_atomic_fetch_add(&ctr->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
@@ -974,17 +974,20 @@ __device__ inline V quad_get(V v) {
     }
 }
 // acc -= sum_c val[e][r][c] * x[3 col[e] + c] over the blocks [lo, hi) of a
-// row, ascending, once the entries of x are there.  The wave's rows wait
-// together (they meet again behind the loop anyway), so the loop and its
-// exit are scalar; NB blocks a pass, absent ones zero (acc - 0 keeps acc),
-// so that no branch separates the products.
+// row, ascending, once the entries of x are there; own (may be NULL): an
+// entry acc waits for besides, whose value it starts from.  The wave's rows
+// wait together (they meet again behind the loop anyway), so the loop and
+// its exit are scalar; NB blocks a pass, absent ones zero, so that no branch
+// separates the products.
 template <int NB, typename T, typename TX>
 __device__ inline T flow_pass(const int32_t *__restrict__ col, const T *__restrict__ val, int e, int hi, int r,
-                              const TX *x, T acc, SweepCtr *ctr, int spin) {
+                              const TX *x, const T *own, T acc, SweepCtr *ctr, int spin) {
     using Bits = typename FlowBits<TX>::type;
+    using OwnBits = typename FlowBits<T>::type;
     int j[NB];
     T b[NB][3];
     Bits xv[NB];
+    OwnBits ov = 0;
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
         j[u] = -1;
@@ -998,13 +1001,16 @@ __device__ inline T flow_pass(const int32_t *__restrict__ col, const T *__restri
     int spins = 0;
     for (;;) {
         bool miss = false;
+        if (own) ov = flow_load(own);
 #pragma unroll
         for (int u = 0; u < NB; ++u) xv[u] = flow_load(x + max(j[u], 0));
+        if (own) miss = ov == FlowBits<T>::mark;
 #pragma unroll
         for (int u = 0; u < NB; ++u) miss |= (j[u] >= 0) & (xv[u] == FlowBits<TX>::mark);
         if (!__any(miss) || flow_give_up(ctr, spins, spin)) break;
         asm volatile("" ::: "memory");
     }
+    if (own) acc = __builtin_bit_cast(T, ov);
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
         const T v = j[u] >= 0 ? (T)__builtin_bit_cast(TX, xv[u]) : (T)0;
@@ -1015,8 +1021,21 @@ __device__ inline T flow_pass(const int32_t *__restrict__ col, const T *__restri
 template <typename T, typename TX>
 __device__ inline T flow_walk(const int32_t *__restrict__ col, const T *__restrict__ val, int lo, int hi, int r,
                               const TX *x, T acc, SweepCtr *ctr, int spin) {
-    if (!__any(hi - lo > 3)) return flow_pass<3>(col, val, lo, hi, r, x, acc, ctr, spin);
-    for (int e = lo; __any(e < hi); e += 4) acc = flow_pass<4>(col, val, e, hi, r, x, acc, ctr, spin);
+    const T *none = nullptr;
+    if (!__any(hi - lo > 3)) return flow_pass<3>(col, val, lo, hi, r, x, none, acc, ctr, spin);
+    for (int e = lo; __any(e < hi); e += 4)
+        acc = flow_pass<4>(col, val, e, hi, r, x, none, acc, ctr, spin);
+    return acc;
+}
+// The same with passes of NB blocks after a first of four.
+template <int NB, typename T, typename TX>
+__device__ inline T flow_walk_wide(const int32_t *__restrict__ col, const T *__restrict__ val, int lo, int hi, int r,
+                                   const TX *x, const T *own, T acc, SweepCtr *ctr, int spin) {
+    if (!__any(hi - lo > 4)) return flow_pass<4>(col, val, lo, hi, r, x, own, acc, ctr, spin);
+    for (int e = lo; __any(e < hi); e += NB) {
+        acc = flow_pass<NB>(col, val, e, hi, r, x, own, acc, ctr, spin);
+        own = nullptr;
+    }
     return acc;
 }
 
@@ -1542,6 +1561,344 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kRo
     }
 }
 
+// --------------------------------- an application and its product at once
+
+// One launch for a preconditioner application and the product with A' that
+// follows it, z = M^-1 in and out = A' z, for systems whose kernels are
+// bound by their launches and by latency: lower rows, upper rows and rows of
+// the product wait on one another as the rows of a single-launch sweep do
+// (see there), so a level costs a store and a load instead of a launch, and
+// the blocks of later rows are loaded while earlier ones are computed.  Row
+// by row the arithmetic of k_lsweep, k_usweep, k_usweep_spmv, k_spmv,
+// k_spmv_lp and k_lower_parts, and their dot-product partials (apply_sums):
+// the launch gives the bits those launches give, so which of the two runs is
+// a matter of time alone.
+//
+// Items in ticket order: lower tiles, upper tiles (rows with upper blocks;
+// the others finish in the lower tile), product tiles, of R rows in one
+// level each.  R is a whole number of the row kernels' workgroups (84, 42 or
+// 21 rows), so a tile holds whole partials.  The large tile is a workgroup
+// of 16 waves: the tickets, about 11 ns each on one address, stay cheap
+// against the work.
+// On entry y and z hold the mark everywhere; y_next and z_next (may be NULL)
+// are marked for the launch that uses them next.
+// MODE: SPMV_V / SPMV_T: out with the dot products (w1, out), (out, out);
+// SPMV_RUN: out alone; SPMV_PLAIN: no product.
+template <typename T>
+struct ApplyArgs {
+    const T *L, *U, *Dinv;
+    const double *Ap, *in;
+    T *y, *y_next;
+    double *z, *z_next;
+    const double *r, *v;   // with FUSE_P: p = r + beta (p - omega v) is the input
+    double *p;
+    double *out;
+    const double *w1;
+    double *P;             // lower parts (see k_spmv_lp)
+    double *part, *fpart;  // partials of the product's rows [r0, n) and of the fused upper rows
+    size_t part_stride, fpart_stride;
+    uint32_t *tk, *ftk;
+    size_t tk_stride, ftk_stride, vstride;
+    SysState *st;
+    SweepCtr *ctr, *next;
+    const int32_t *lt, *ut;   // first rows of the lower and the upper tiles
+    int nsys, spin, nl, nu, np, u0_end;
+    int uf0, nf;       // upper tiles [uf0, uf0 + nf): the rows [0, fuse_n0), read from A'
+    int r0;            // the product's first row: fuse_n0 when the upper tiles form the others', else 0
+    int vw;            // waves of the row kernels' workgroups whose partials are formed
+    int lp_out, lp_in; // form the lower parts for the next application; take this one's
+};
+
+// The sums of a tile's dot products as the row kernels leave them: sv holds
+// the terms of each row component, virtual wave w adds rows [21 w, 21 w + 21)
+// of the tile, vw of them make a workgroup's partial, 32 partials a group
+// sum (group_reduce).  Called by the whole workgroup.
+template <int R>
+__device__ inline void apply_sums(const double (&sv)[2][3 * R], int tile, int vw, int nblk, double *part,
+                                  uint32_t *tickets) {
+    constexpr int NW = R / kRowsPerWave;
+    __shared__ double sw[2][NW];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    __syncthreads();
+    if (w < NW)
+        for (int k = 0; k < 2; ++k) {
+            const double s = wave_sum(lane < 63 ? sv[k][63 * w + lane] : 0.0);
+            if (lane == 0) sw[k][w] = s;
+        }
+    __syncthreads();
+    const int bx = tile * (NW / vw) + w;
+    if (w >= NW / vw || bx >= nblk) return;
+    const int g = bx / kGroup, gsize = min(kGroup, nblk - g * kGroup);
+    uint32_t t = 0;
+    if (lane == 0) {
+        for (int k = 0; k < 2; ++k) {
+            double s = 0.0;
+            for (int i = 0; i < vw; ++i) s += sw[k][w * vw + i];
+            __hip_atomic_store(part + (size_t)bx * 2 + k, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        t = __hip_atomic_fetch_add(tickets + (size_t)kTicketPad * (1 + g), 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(t) != (uint32_t)(gsize - 1)) return;
+    double gs[2];
+    for (int k = 0; k < 2; ++k)
+        gs[k] = wave_sum(lane < gsize ? __hip_atomic_load(part + (size_t)(g * kGroup + lane) * 2 + k, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT)
+                                      : 0.0);
+    if (lane == 0) {
+        __hip_atomic_store(tickets + (size_t)kTicketPad * (1 + g), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int k = 0; k < 2; ++k) part[(size_t)nblk * 2 + (size_t)g * 2 + k] = gs[k];
+    }
+}
+
+// Up to NB blocks [e, hi) of a row of A' against z, ascending, added to the
+// product's sum av and, with SUB, subtracted from the sweep's sum acc (in T).
+// LP: also pa, pb += the blocks of columns below r0 times P's two vectors,
+// which their rows store before z.
+template <int NB, bool SUB, bool LP, typename T>
+__device__ inline void apply_pass(const int32_t *__restrict__ col, const double *__restrict__ val, int e, int hi, int r,
+                                  const double *z, const T *own, T &acc, double &av, const double *P, int r0,
+                                  double &pa, double &pb, SweepCtr *ctr, int spin) {
+    using OwnBits = typename FlowBits<T>::type;
+    int j[NB];
+    double b[NB][3];
+    uint64_t xv[NB];
+    OwnBits ov = 0;
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        j[u] = -1;
+        b[u][0] = b[u][1] = b[u][2] = 0.0;
+        if (e + u < hi) {
+            j[u] = col[e + u];
+            const double *bp = val + (size_t)(e + u) * 9 + 3 * r;
+            b[u][0] = bp[0]; b[u][1] = bp[1]; b[u][2] = bp[2];
+        }
+    }
+    int spins = 0;
+    for (;;) {
+        bool miss = false;
+        if (SUB && own) ov = flow_load(own);
+#pragma unroll
+        for (int u = 0; u < NB; ++u) xv[u] = flow_load(z + 3 * max(j[u], 0) + r);
+        if (SUB && own) miss = ov == FlowBits<T>::mark;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) miss |= (j[u] >= 0) & (xv[u] == FlowBits<double>::mark);
+        if (!__any(miss) || flow_give_up(ctr, spins, spin)) break;
+        asm volatile("" ::: "memory");
+    }
+    if (SUB && own) acc = __builtin_bit_cast(T, ov);
+#pragma unroll
+    for (int h = 0; h < NB; h += 4) {
+        double pv[4][2];
+        if constexpr (LP) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                pv[u][0] = pv[u][1] = 0.0;
+                if (j[h + u] >= 0 && j[h + u] < r0) {
+                    const double *pj = P + 6 * (size_t)j[h + u] + r;
+                    pv[u][0] = __builtin_bit_cast(double, flow_load(pj));
+                    pv[u][1] = __builtin_bit_cast(double, flow_load(pj + 3));
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double (&bb)[3] = b[h + u];
+            const double x = j[h + u] >= 0 ? __builtin_bit_cast(double, xv[h + u]) : 0.0;
+            const double x0 = quad_get<0>(x), x1 = quad_get<1>(x), x2 = quad_get<2>(x);
+            av += dot3(bb[0], bb[1], bb[2], x0, x1, x2);
+            if constexpr (SUB) acc -= dot3((T)bb[0], (T)bb[1], (T)bb[2], (T)x0, (T)x1, (T)x2);
+            if constexpr (LP) {
+                pa += dot3(bb[0], bb[1], bb[2], quad_get<0>(pv[u][0]), quad_get<1>(pv[u][0]), quad_get<2>(pv[u][0]));
+                pb += dot3(bb[0], bb[1], bb[2], quad_get<0>(pv[u][1]), quad_get<1>(pv[u][1]), quad_get<2>(pv[u][1]));
+            }
+        }
+    }
+}
+
+template <typename T, int MODE, bool FUSE_P, int W, int R>
+__global__ void __launch_bounds__(64 * W) k_apply_flow(DevSchedule d, ApplyArgs<T> a) {
+    static_assert(R <= kFlowRowsPerWave * W && R % (kRowsPerWave * kWavesPerBlock) == 0, "tile rows");
+    constexpr bool DOTS = MODE == SPMV_V || MODE == SPMV_T;
+    // a row of a 7-point grid in one pass, all its loads before its first
+    // wait, where the registers allow it (16 waves leave 128 a lane)
+    constexpr int NB = W < 8 ? 8 : 4;
+    // lower parts: FP64 factors, formed by BiCGStab's first application
+    constexpr bool LPO = sizeof(T) == sizeof(double) && MODE == SPMV_V;
+    constexpr bool LPI = sizeof(T) == sizeof(double) && MODE == SPMV_T;
+    __shared__ double sv[2][DOTS ? 3 * R : 1];
+    flow_clear(a.next);
+    if (a.st && a.nsys == 1 && a.st[0].phase != PH_RUN) return;
+    // the row's terms of the dot products
+    auto terms = [&](int row, int r, bool own, double w, double o) {
+        if constexpr (DOTS)
+            if (own && row < R) {
+                sv[0][3 * row + r] = w * o;
+                sv[1][3 * row + r] = o * o;
+            }
+    };
+    flow_items<W>(a.ctr, (a.nl + a.nu + a.np) * a.nsys, a.nsys, [&](int tile, int sys) {
+        if (a.st && a.st[sys].phase != PH_RUN) return;
+        const size_t vo = (size_t)sys * a.vstride;
+        const double *Aps = a.Ap + (size_t)sys * d.nnzb * 9;
+        const int row = (int)(threadIdx.x >> 2);   // in the tile
+        if (tile < a.nl) {
+            const FlowLane fl = flow_lane(a.lt[tile]);
+            if (fl.q >= a.lt[tile + 1]) return;
+            const int i = d.lrows[fl.q];
+            const size_t k = vo + 3 * (size_t)i + fl.r;
+            const int uq = d.l2u[fl.q];
+            T acc;
+            if (FUSE_P) {
+                const double beta = a.st[sys].beta, omega = a.st[sys].omega;
+                const double p = a.r[k] + beta * (a.p[k] - omega * a.v[k]);
+                if (fl.own) a.p[k] = p;
+                acc = (T)p;
+            } else {
+                acc = (T)a.in[k];
+            }
+            if (fl.own) {
+                if (a.y_next) flow_mark(a.y_next + k);
+                if (a.z_next) flow_mark(a.z_next + k);
+            }
+            const bool lp = LPI && a.lp_in;
+            if (lp && i < d.fuse_n0) return;   // y is the input itself
+            T dq[3] = {0, 0, 0};
+            if (uq < a.u0_end) {
+                const T *dp = a.Dinv + ((size_t)sys * d.n + uq) * 9 + 3 * fl.r;
+                dq[0] = dp[0]; dq[1] = dp[1]; dq[2] = dp[2];
+            }
+            if (lp) {
+                const double *pp = a.P + 2 * vo + 6 * (size_t)i + fl.r;
+                const double alpha = a.st[sys].alpha;
+                acc = (T)((double)acc - (pp[0] - alpha * pp[3]));
+            } else {
+                const T *none = nullptr;
+                acc = flow_walk_wide<NB>(d.lcol, a.L + (size_t)sys * d.nL * 9, d.lptr[fl.q], d.lptr[fl.q + 1], fl.r,
+                                     (const T *)a.y + vo, none, acc, a.ctr, a.spin);
+            }
+            const double zr = (double)dot3(dq[0], dq[1], dq[2], quad_get<0>(acc), quad_get<1>(acc), quad_get<2>(acc));
+            if (fl.own) {
+                if (!lp) flow_store<false>(a.y + k, acc);
+                if (uq < a.u0_end) flow_store<false>(a.z + k, zr);
+            }
+            return;
+        }
+        const double *zs = (const double *)a.z + vo;
+        double none_a = 0.0, none_b = 0.0;
+        if (tile < a.nl + a.nu) {
+            const int t = tile - a.nl;
+            const FlowLane fl = flow_lane(a.ut[t]);
+            const bool act = fl.q < a.ut[t + 1];
+            if (t < a.uf0 || t >= a.uf0 + a.nf) {
+                if (!act) return;
+                const size_t k = vo + 3 * (size_t)d.urows[fl.q] + fl.r;
+                const T *dp = a.Dinv + ((size_t)sys * d.n + fl.q) * 9 + 3 * fl.r;
+                const T d0 = dp[0], d1 = dp[1], d2 = dp[2];
+                const T acc = flow_walk_wide<NB>(d.ucol, a.U + (size_t)sys * d.nU * 9, d.uptr[fl.q], d.uptr[fl.q + 1],
+                                             fl.r, zs, (const T *)a.y + k, (T)0, a.ctr, a.spin);
+                const double zr = (double)dot3(d0, d1, d2, quad_get<0>(acc), quad_get<1>(acc), quad_get<2>(acc));
+                if (fl.own) flow_store<false>(a.z + k, zr);
+                return;
+            }
+            // rows [0, fuse_n0), from their rows of A': the sweep's row and,
+            // when the product starts behind them, the product's
+            const int i = fl.q - d.fuse_q0;
+            double w = 0.0, av = 0.0;
+            if (act) {
+                const size_t k = vo + 3 * (size_t)i + fl.r;
+                const T *dp = a.Dinv + ((size_t)sys * d.n + fl.q) * 9 + 3 * fl.r;
+                const T d0 = dp[0], d1 = dp[1], d2 = dp[2];
+                const int e0 = d.prow[i], e1 = d.prow[i + 1];
+                const double *dg = Aps + (size_t)e0 * 9 + 3 * fl.r;
+                const double g0 = dg[0], g1 = dg[1], g2 = dg[2];
+                const bool product = a.r0 > 0;
+                if (DOTS && product) w = a.w1[k];
+                const bool lpo = LPO && a.lp_out;
+                const double rk = lpo ? a.r[k] : 0.0;
+                const T *own = LPI && a.lp_in ? nullptr : (const T *)a.y + k;
+                T acc = own ? (T)0 : (T)a.in[k];
+                for (int e = e0 + 1; __any(e < e1); e += NB) {
+                    apply_pass<NB, true, false>(d.pcol, Aps, e, e1, fl.r, zs, own, acc, av, (const double *)nullptr, 0,
+                                            none_a, none_b, a.ctr, a.spin);
+                    own = nullptr;
+                }
+                const double zr = (double)dot3(d0, d1, d2, quad_get<0>(acc), quad_get<1>(acc), quad_get<2>(acc));
+                av += dot3(g0, g1, g2, quad_get<0>(zr), quad_get<1>(zr), quad_get<2>(zr));
+                if constexpr (LPO) {
+                    if (lpo) {
+                        const double pr = dot3((double)d0, (double)d1, (double)d2, quad_get<0>(rk), quad_get<1>(rk),
+                                               quad_get<2>(rk));
+                        const double pv = dot3((double)d0, (double)d1, (double)d2, quad_get<0>(av), quad_get<1>(av),
+                                               quad_get<2>(av));
+                        if (fl.own) {
+                            double *pp = a.P + 2 * vo + 6 * (size_t)i + fl.r;
+                            __hip_atomic_store(pp, pr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            __hip_atomic_store(pp + 3, pv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        }
+                        // in place before z appears
+                        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                        __builtin_amdgcn_s_waitcnt(0);
+                        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                    }
+                }
+                if (fl.own) {
+                    flow_store<false>(a.z + k, zr);
+                    if (product) a.out[k] = av;
+                }
+            }
+            if constexpr (DOTS) {
+                if (a.r0 == 0) return;
+                terms(row, fl.r, fl.own, w, act ? av : 0.0);
+                apply_sums<R>(sv, t - a.uf0, a.vw, (d.fuse_n0 + a.vw * kRowsPerWave - 1) / (a.vw * kRowsPerWave),
+                              a.fpart + sys * a.fpart_stride, a.ftk + sys * a.ftk_stride);
+            }
+            return;
+        }
+        if constexpr (MODE != SPMV_PLAIN) {
+            const int t = tile - a.nl - a.nu;
+            const FlowLane fl = flow_lane(a.r0 + t * R);
+            const bool act = fl.q < d.n && row < R;
+            double w = 0.0, av = 0.0;
+            if (act) {
+                const size_t k = vo + 3 * (size_t)fl.q + fl.r;
+                const int e0 = d.prow[fl.q], e1 = d.prow[fl.q + 1];
+                if (DOTS) w = a.w1[k];
+                const bool lpo = LPO && a.lp_out;
+                double pa = 0.0, pb = 0.0;
+                const double *none = nullptr;
+                for (int e = e0; __any(e < e1); e += NB) {
+                    if constexpr (LPO) {
+                        if (lpo) {
+                            apply_pass<NB, false, true>(d.pcol, Aps, e, e1, fl.r, zs, none, none_a, av,
+                                                    (const double *)a.P + 2 * vo, a.r0, pa, pb, a.ctr, a.spin);
+                            continue;
+                        }
+                    }
+                    apply_pass<NB, false, false>(d.pcol, Aps, e, e1, fl.r, zs, none, none_a, av, none, 0, pa, pb, a.ctr,
+                                             a.spin);
+                }
+                if (fl.own) {
+                    a.out[k] = av;
+                    if (lpo) {
+                        double *pp = a.P + 2 * vo + 6 * (size_t)fl.q + fl.r;
+                        pp[0] = pa;
+                        pp[3] = pb;
+                    }
+                }
+            }
+            if constexpr (DOTS) {
+                terms(row, fl.r, fl.own, w, av);
+                apply_sums<R>(sv, t, a.vw, (d.n - a.r0 + a.vw * kRowsPerWave - 1) / (a.vw * kRowsPerWave),
+                              a.part + sys * a.part_stride, a.tk + sys * a.tk_stride);
+            }
+        }
+    });
+}
+
 // ------------------------------------- upper sweep fused with the product
 
 // LDS capacity (blocks of A') per wave of the fused upper launch.
@@ -1840,7 +2197,7 @@ __global__ void __launch_bounds__(kTotalThreads) k_spmv_total(double *__restrict
 __global__ void __launch_bounds__(kVecThreads) k_setup(int n, const int32_t *__restrict__ perm,
                                                        const double *__restrict__ b, Krylov k,
                                                        const int32_t *__restrict__ bad, double reduction,
-                                                       int max_iter) {
+                                                       int max_iter, int flow) {
     const int sys = blockIdx.y, bx = blockIdx.x;
     const size_t vo = (size_t)sys * k.vstride, bo = (size_t)sys * 3 * n, m = 3 * (size_t)n;
     const size_t tiles = k.vstride / kVecTile;
@@ -1857,6 +2214,12 @@ __global__ void __launch_bounds__(kVecThreads) k_setup(int n, const int32_t *__r
             const size_t e = vo + t * kVecTile + u * kVecThreads + threadIdx.x;
             k.r[e] = val[u]; k.rhat[e] = val[u];
             k.x[e] = 0.0; k.p[e] = 0.0; k.v[e] = 0.0;
+            // k_apply_flow's first application finds both marked: all of y
+            // (of either factor type), phat but for its padding of zeros
+            if (flow) {
+                flow_mark((double *)k.y + e);
+                if (e - vo < m) flow_mark(k.phat + e);
+            }
             v[0] += val[u] * val[u];
         }
     }
@@ -1966,8 +2329,9 @@ __global__ void __launch_bounds__(kVecThreads) k_s_update(Krylov k, int sums_at,
 
 // Full step: x += alpha phat + omega shat, r = s - omega t, ||r||, (rhat, r),
 // full-step test, next rho and beta.  After a half-step stop (or an omega
-// breakdown) only x += alpha phat.
-__global__ void __launch_bounds__(kVecThreads) k_xr_update(Krylov k, int sums_at, int sums, int fsums_at, int fsums) {
+// breakdown) only x += alpha phat.  flow: entries of phat to mark (0: none).
+__global__ void __launch_bounds__(kVecThreads) k_xr_update(Krylov k, int sums_at, int sums, int fsums_at, int fsums,
+                                                           int flow) {
     const int sys = blockIdx.y, bx = blockIdx.x;
     const size_t vo = (size_t)sys * k.vstride, tiles = k.vstride / kVecTile;
     // the first tile's vectors are requested before the state and the
@@ -2047,6 +2411,7 @@ __global__ void __launch_bounds__(kVecThreads) k_xr_update(Krylov k, int sums_at
             for (int u = 0; u < kVecItems; ++u) {
                 const size_t e = e0 + u * kVecThreads;
                 k.x[e] = xv[u] + (alpha * ph[u] + omega * sh[u]);
+                if (e - vo < (size_t)flow) flow_mark(k.phat + e);   // for the next iteration's k_apply_flow
                 const double r = sv[u] - omega * tv[u];
                 k.r[e] = r;
                 v[0] += r * r;
@@ -2618,8 +2983,9 @@ void launch_spmv(int n, const int32_t *ptr, const int32_t *col, const double *A,
 }
 
 void launch_setup(const DevSchedule &d, const double *b_orig, const int32_t *bad, double reduction, int max_iter,
-                  Krylov &k, int nsys, hipStream_t s) {
-    k_setup<<<dim3(vec_blocks(d.n), nsys), kVecThreads, 0, s>>>(d.n, d.perm, b_orig, k, bad, reduction, max_iter);
+                  Krylov &k, int nsys, bool flow, hipStream_t s) {
+    k_setup<<<dim3(vec_blocks(d.n), nsys), kVecThreads, 0, s>>>(d.n, d.perm, b_orig, k, bad, reduction, max_iter,
+                                                                flow ? 1 : 0);
 }
 
 void launch_spmv_v(const DevSchedule &d, const double *Ap, size_t a_stride, Krylov &k, int nsys, int variant,
@@ -2650,6 +3016,58 @@ void launch_s_update(const DevSchedule &d, Krylov &k, int nsys, int spmv_variant
               f.offset, f.count);
 }
 
+// Whether k_apply_flow takes tiles of kApplyRowsSmall rows (6 waves) instead
+// of kApplyRows (16), by the rows of a level (of all systems): small tiles
+// spread a narrow level over more CUs and leave registers for whole rows in
+// one pass, large ones cost a third of the tickets.  Solves with small
+// against large tiles: 10 000 cells, two colours 200 and 210 us; 15 000 cells
+// with NNCs, four colours 254 and 281; 96k cells with NNCs, 33 RCM levels 571
+// and 749, four colours 455 and 387; 50 000 cells, two colours, FP32 factors
+// 276 and 245.
+constexpr int kApplySmallRows = 10000;
+
+template <typename T>
+void launch_apply_flow(const DevSchedule &d, const T *L, const T *U, const T *Dinv, const double *Ap,
+                       const double *in, T *y, T *y_next, double *z, double *z_next, double *out, const double *w1,
+                       Krylov &k, SysState *st, SweepCtr *ctr, SweepCtr *next, int u0_end, int nsys, int mode,
+                       bool fused, bool lp, int spmv_variant, int levels, int grid, int spin, hipStream_t s,
+                       hipEvent_t ev0, hipEvent_t ev1) {
+    if (d.n <= 0 || nsys <= 0) return;
+    const bool small = (long long)d.n * nsys <= (long long)kApplySmallRows * levels;
+    const int rows = small ? kApplyRowsSmall : kApplyRows;
+    const DevSchedule::ApplyTiles &t = small ? d.tiles_small : d.tiles_large;
+    const int r0 = fused && mode != APPLY_ONLY ? d.fuse_n0 : 0;
+    ApplyArgs<T> a{L, U, Dinv, Ap, in, y, y_next, z, z_next, k.r, k.v, k.p, out, w1, k.lp, k.spart, k.fpart,
+                   k.spart_stride, k.fpart_stride, k.tickets, k.ftickets, k.ticket_stride, k.fticket_stride,
+                   k.vstride, st, ctr, next, t.lt, t.ut, nsys, spin, t.nl, t.nu,
+                   mode == APPLY_ONLY ? 0 : (d.n - r0 + rows - 1) / rows, u0_end, t.uf0, t.nf, r0,
+                   variant_waves(spmv_variant), lp && mode == APPLY_V ? 1 : 0, lp && mode == APPLY_T ? 1 : 0};
+    const dim3 g(std::max(1, std::min(grid, (a.nl + a.nu + a.np) * nsys))), b(small ? 64 * 6 : 64 * 16);
+    auto go = [&](auto MODE, auto FUSE) {
+        constexpr int m = decltype(MODE)::value;
+        constexpr bool f = decltype(FUSE)::value;
+        if (small) launch_ev(k_apply_flow<T, m, f, 6, kApplyRowsSmall>, g, b, s, ev0, ev1, d, a);
+        else launch_ev(k_apply_flow<T, m, f, 16, kApplyRows>, g, b, s, ev0, ev1, d, a);
+    };
+    using F = std::false_type;
+    switch (mode) {
+    case APPLY_V: go(std::integral_constant<int, SPMV_V>{}, std::true_type{}); break;
+    case APPLY_T: go(std::integral_constant<int, SPMV_T>{}, F{}); break;
+    case APPLY_RUN: go(std::integral_constant<int, SPMV_RUN>{}, F{}); break;
+    default: go(std::integral_constant<int, SPMV_PLAIN>{}, F{}); break;
+    }
+}
+template void launch_apply_flow<double>(const DevSchedule &, const double *, const double *, const double *,
+                                        const double *, const double *, double *, double *, double *, double *,
+                                        double *, const double *, Krylov &, SysState *, SweepCtr *, SweepCtr *, int,
+                                        int, int, bool, bool, int, int, int, int, hipStream_t, hipEvent_t,
+                                        hipEvent_t);
+template void launch_apply_flow<float>(const DevSchedule &, const float *, const float *, const float *,
+                                       const double *, const double *, float *, float *, double *, double *,
+                                       double *, const double *, Krylov &, SysState *, SweepCtr *, SweepCtr *, int,
+                                       int, int, bool, bool, int, int, int, int, hipStream_t, hipEvent_t,
+                                        hipEvent_t);
+
 void launch_p_update(const DevSchedule &d, Krylov &k, int nsys, hipStream_t s) {
     const int m = 3 * d.fuse_n0;
     if (m <= 0 || nsys <= 0) return;
@@ -2664,12 +3082,12 @@ void launch_spmv_t(const DevSchedule &d, const double *Ap, size_t a_stride, Kryl
 }
 
 void launch_xr_update(const DevSchedule &d, Krylov &k, int nsys, int spmv_variant, int split, bool fused,
-                      hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, bool fix) {
+                      hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, bool fix, bool flow) {
     const SpmvSums at = spmv_sums(d.n - (fused ? d.fuse_n0 : 0), variant_waves(spmv_variant), split);
     SpmvSums f = fused_sums(d, fused, spmv_variant);
     if (fused && fix) ++f.count;
     launch_ev(k_xr_update, dim3(vec_blocks(d.n), nsys), dim3(kVecThreads), s, ev0, ev1, k, at.offset, at.count,
-              f.offset, f.count);
+              f.offset, f.count, flow ? 3 * d.n : 0);
 }
 
 template <typename T>

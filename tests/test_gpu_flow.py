@@ -121,3 +121,65 @@ def test_single_launch_factorisation_reports_a_zero_pivot():
         assert st == rs.ZERO_PIVOT and bad[0] == row
         st, bad = s.factor(_pattern("grid16x8x8")[2])
         assert st == rs.OK and bad[0] == -1
+
+
+APPLY_PATTERNS = ["diag_1", "diag_65", "chain_2", "chain_257", "dense_9", "dense_40", "grid7x5x3", "grid16x8x8",
+                  "grid23x17x15", "grid19x18x18", "nnc", "big_nnc", "ensemble"]
+
+
+@pytest.mark.parametrize("variant", [0, 4, 8])
+@pytest.mark.parametrize("precision", [rs.PREC_FP64, rs.PREC_FP32_FACTORS])
+@pytest.mark.parametrize("ordering", [rs.ORDER_GRAPH_COLOUR, rs.ORDER_RCM_LEVEL_SET])
+@pytest.mark.parametrize("name", APPLY_PATTERNS)
+def test_application_and_product_in_one_launch(name, ordering, precision, variant):
+    """BiCGStab whose applications and products are one launch each (small
+    systems) against the separate launches (which a solve takes while its
+    sweeps are timed): the same bits, for tiles of 84 rows (up to 6 000 rows)
+    and of 252, filled exactly or not, every number of waves a partial, with
+    and without fused rows and lower parts, and with graphs off (separate
+    launches again), after a solve that stopped at its iteration limit."""
+    if name == "big_nnc":
+        s = make_grid_system(31, 23, 12, active_frac=0.9, nnc_frac=0.03, seed=6)
+        rowptr, colidx, vals = s.rowptr, s.colidx, s.vals
+    else:
+        rowptr, colidx, vals = _pattern(name)
+    n, batch = len(rowptr) - 1, vals.shape[0]
+    b = np.random.default_rng(8).standard_normal((batch, n, 3))
+
+    def outcomes(s, red, max_iter):
+        x, st, info = s.solve(b, reduction=red, max_iter=max_iter)
+        return x, st, [(i["status"], i["half_steps"], i["final_norm"], i["true_rel_residual"]) for i in info]
+
+    with rs.Solver(rowptr, colidx, vals, ordering=ordering, precision=precision) as s:
+        rs.ilu0_set_option(s.M, rs.OPT_SPMV_VARIANT, variant)
+        s.factor()
+        for red, max_iter in ((0.0, 3), (1e-8, 200)):
+            rs.rsolve_profile_enable(1 << rs.PROF_LSWEEP)
+            try:
+                want = outcomes(s, red, max_iter)
+                assert rs.rsolve_profile_get(rs.PROF_LSWEEP)[1] > 0
+            finally:
+                rs.rsolve_profile_enable(0)
+            for graph in (0, 1, 1):
+                rs.ilu0_set_option(s.M, rs.OPT_USE_GRAPH, graph)
+                got = outcomes(s, red, max_iter)
+                assert np.array_equal(got[0], want[0], equal_nan=True) and got[1:] == want[1:]
+
+
+def test_one_launch_application_recovers_from_a_wait_that_gives_up():
+    s = make_grid_system(17, 13, 9, active_frac=0.85, nnc_frac=0.03, seed=4)
+    b = s.b[:, 0]
+    with rs.Solver(s.rowptr, s.colidx, s.vals, ordering=rs.ORDER_GRAPH_COLOUR) as sol:
+        sol.factor()
+        want, st, _ = sol.solve(b)
+        assert st == rs.OK
+        default = rs.ilu0_get_option(sol.M, rs.OPT_SPIN_LIMIT)
+        rs.ilu0_set_option(sol.M, rs.OPT_SPIN_LIMIT, 0)
+        with pytest.raises(rs.RsolveError) as e:
+            for _ in range(5):
+                sol.solve(b)
+        assert e.value.status == rs.HIP_ERROR
+        rs.ilu0_set_option(sol.M, rs.OPT_SPIN_LIMIT, default)
+        for _ in range(2):
+            x, st, _ = sol.solve(b)
+            assert st == rs.OK and np.array_equal(x, want)
