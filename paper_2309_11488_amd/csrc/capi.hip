@@ -238,11 +238,11 @@ struct rs_ilu0 {
     DevBuf pvals, L, U, Dinv, Lf, Uf, Dinvf, bad;
     std::vector<int32_t> bad_host;
     // solve workspace
-    DevBuf work, ywork, ywork2, ftickets, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
+    DevBuf work, ywork, ywork2, ftickets, vpart, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
     bool y_marked = false;     // ywork holds the mark everywhere (single-launch sweeps)
     Krylov k{};
     // GMRES workspace: Krylov basis, per-system cycle state, reduction partials
-    DevBuf gm_basis, gm_state, gm_part;
+    DevBuf gm_basis, gm_state, gm_part, gm_vpart;
     int last_gm_steps = 1;
     SysState *h_state = nullptr;
     rs::SweepCtr *h_ctr = nullptr;
@@ -1022,8 +1022,16 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
         HIP_TRY(M->ctrs.alloc(2 * sizeof(rs::SweepCtr)));
         HIP_TRY(hipMemsetAsync(M->ctrs.p, 0, 2 * sizeof(rs::SweepCtr), s));
     }
+    const size_t vps = 2 * (size_t)rs::vec_blocks(M->n);
+    if (!M->vpart.p) {
+        HIP_TRY(M->vpart.alloc(B * vps * sizeof(double)));
+        rs::launch_flow_mark(M->vpart.p, B * vps * sizeof(double), s);
+        HIP_TRY(hipGetLastError());
+    }
     double *w = M->work.as<double>();
     Krylov &k = M->k;
+    k.vpart = M->vpart.as<double>();
+    k.vpart_stride = vps;
     k.r = w; k.rhat = w + vec; k.p = w + 2 * vec; k.v = w + 3 * vec; k.phat = w + 4 * vec;
     k.s = w + 5 * vec; k.shat = w + 6 * vec; k.t = w + 7 * vec; k.x = w + 8 * vec;
     k.vstride = vs;
@@ -1963,8 +1971,14 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
     }
     HIP_TRY(M->gm_state.alloc((size_t)B * sizeof(rs::GmState)));
     HIP_TRY(M->gm_part.alloc((size_t)B * rs::gm_part_stride() * sizeof(double)));
+    if (!M->gm_vpart.p) {
+        const size_t bytes = (size_t)B * rs::gm_poll_stride() * sizeof(double);
+        HIP_TRY(M->gm_vpart.alloc(bytes));
+        rs::launch_flow_mark(M->gm_vpart.p, bytes, s);
+        HIP_TRY(hipGetLastError());
+    }
     rs::GmWork g{M->gm_basis.as<double>(), colstride, k.vstride, M->gm_part.as<double>(), rs::gm_part_stride(),
-                 k.tickets, k.ticket_stride, M->gm_state.as<rs::GmState>(), k.st};
+                 k.tickets, k.ticket_stride, M->gm_vpart.as<double>(), M->gm_state.as<rs::GmState>(), k.st};
     const size_t m = 3 * (size_t)M->n * B;
     const double *bd = nullptr;
     st = stage_in(b, mem, M->bstage, m, s, &bd);

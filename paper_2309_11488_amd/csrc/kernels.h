@@ -94,6 +94,8 @@ struct Krylov {
     void *y2;           // a second one (single-launch applications, else NULL)
     double *part;       // reduction partials, nsys * part_stride
     size_t part_stride;
+    double *vpart;      // partials of the vector kernels, marked between launches, nsys * vpart_stride
+    size_t vpart_stride;
     uint32_t *tickets;  // reduction ticket counters, nsys * ticket_stride
     size_t ticket_stride;
     uint32_t *ftickets; // counters of the fused upper rows' partials in launch_apply_flow
@@ -375,9 +377,12 @@ struct GmWork {
     size_t pstride;
     uint32_t *tickets;   // reduction counters, tkstride per system
     size_t tkstride;
+    double *vpart;       // partials that a workgroup polls (marked between launches), gm_poll_stride per system
     GmState *gm;
     SysState *st;
 };
+constexpr int kGmPollBlocks = 512;
+constexpr size_t gm_poll_stride() { return (size_t)(kGmMax + 1) * kGmPollBlocks; }
 inline size_t gm_part_stride() { return (size_t)(kGmMax + 1) * (kVecMaxBlocks + kVecMaxBlocks / 32 + 1) + 16; }
 
 // GMRES building blocks; each acts on the systems still iterating (phase

@@ -183,3 +183,18 @@ def test_one_launch_application_recovers_from_a_wait_that_gives_up():
         for _ in range(2):
             x, st, _ = sol.solve(b)
             assert st == rs.OK and np.array_equal(x, want)
+
+
+@pytest.mark.parametrize("n", [1, 341, 342, 12_000, 350_000, 720_001])
+def test_polled_reduction_adds_every_partial(n):
+    """||b|| over one workgroup, a second one that holds a single entry, many
+    (up to 1 024: one pass of the polling workgroup), more (several passes)
+    and more tiles than workgroups: a sum of 3n squares is within
+    3n eps of the exact one in any order, so the norm is too; the same twice."""
+    eye = np.tile(np.eye(3), (n, 1, 1))
+    b = np.random.default_rng(n).standard_normal((1, n, 3))
+    with rs.Solver(np.arange(n + 1), np.arange(n), eye, ordering=rs.ORDER_GRAPH_COLOUR) as s:
+        s.factor()
+        norms = [s.solve(b, reduction=0.0, max_iter=0)[2][0]["r0_norm"] for _ in range(2)]
+    want = np.linalg.norm(b)
+    assert norms[0] == norms[1] and abs(norms[0] - want) <= 3 * n * np.finfo(np.float64).eps * want
