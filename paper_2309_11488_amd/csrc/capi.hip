@@ -1299,13 +1299,14 @@ static int class_parts(int mask) {
 // launches would fill (a burst of 24 requests of 10 000 to 200 000 cells on
 // four slots 4.91 against 4.41 ms).
 constexpr long long kFlowRowsMany = 200000, kFlowRowsTwo = 30000, kFlowRowsTwoF32 = 60000;
-static bool flow_iteration(const rs_ilu0 *M) {
+static bool flow_size(const rs_ilu0 *M) {
     const int single = 1 << PC_LSWEEP | 1 << PC_USWEEP | 1 << PC_SPMV_V | 1 << PC_SPMV_T;
     const long long most = !M->an->sch.y_in ? kFlowRowsMany
                            : M->precision == RS_PREC_FP64 ? kFlowRowsTwo : kFlowRowsTwoF32;
-    return M->use_graph && M->fuse_spmv && !M->tile_sweeps && M->split() == 0 && M->wdev.nw == 0 && !(g_prof.mask & single) &&
+    return M->use_graph && M->fuse_spmv && !M->tile_sweeps && M->wdev.nw == 0 && !(g_prof.mask & single) &&
            (long long)M->n * M->batch <= most;
 }
+static bool flow_iteration(const rs_ilu0 *M) { return flow_size(M) && M->split() == 0; }
 // Workgroups of such a launch: as many as fit on the device at once (16
 // waves each, one a CU).
 constexpr int kFlowApplyGrid = 512;
@@ -1842,10 +1843,40 @@ static bool gm_fused(const rs_ilu0 *M) {
     return M->fuse_spmv && M->an->sch.fuse_n0 > 0 && !M->tile_sweeps;
 }
 
+// The vectors of GMRES's single-launch applications: two pairs (y, z) used in
+// turn, each launch marking the other pair for the next one.  (A system that
+// stops skips the launches that follow, so after a cycle's end both start
+// anew from a marked pair.)
+struct GmFlow {
+    bool on = false;
+    int pair = 0;   // the pair that is marked
+    int ctr = 0;    // the counter that is clear (each launch clears the other)
+};
+
+// One such launch: z = M^-1 in and, with mode APPLY_RUN, k.t = A' z.
+// Returns z.
+template <typename T>
+static double *gm_apply_flow(ilu0_t M, const T *L, const T *U, const T *D, const double *in, SysState *st, int mode,
+                             GmFlow &f, hipStream_t s, const ProfScope &ps) {
+    Krylov &k = M->k;
+    T *y[2] = {(T *)k.y, (T *)k.y2};
+    double *z[2] = {k.phat, k.shat};
+    rs::SweepCtr *c[2] = {k.lctr, k.uctr};
+    const int p = f.pair, q = f.ctr;
+    f.pair = 1 - p;
+    f.ctr = 1 - q;
+    rs::launch_apply_flow<T>(M->an->dev, L, U, D, M->pvals.as<double>(), in, y[p], y[1 - p], z[p], z[1 - p], k.t,
+                             nullptr, k, st, c[q], c[1 - q], M->an->sch.uset[1], M->batch, mode, gm_fused(M), false,
+                             M->spmv_variant, M->an->sch.nl_levels, kFlowApplyGrid, M->spin_limit, s, ps.start(),
+                             ps.stop());
+    return z[p];
+}
+
 // Queue one Arnoldi step (column j) of every iterating system on `s`.
 // Timed launches record their own dispatch events.
 template <typename T>
-static void gm_step(ilu0_t M, const T *L, const T *U, const T *D, const rs::GmWork &g, int j, hipStream_t s) {
+static void gm_step(ilu0_t M, const T *L, const T *U, const T *D, const rs::GmWork &g, int j, GmFlow &flow,
+                    hipStream_t s) {
     Krylov &k = M->k;
     const int B = M->batch;
     const double n = M->n, nnzb = M->nnzb, vb = (double)B * 24 * n;
@@ -1855,7 +1886,11 @@ static void gm_step(ilu0_t M, const T *L, const T *U, const T *D, const rs::GmWo
     const double *vj = g.V + (size_t)j * g.colstride;
     const bool fz = gm_fused(M);
     const double fb = fz ? fused_spmv_bytes(M, B) : 0.0;
-    if (fz) {
+    if (flow.on) {
+        ProfScope ps(PC_APPLY, s,
+                     lower_bytes(M, sizeof(T), B) + upper_bytes(M, sizeof(T), B) + B * (76 * nnzb + 52 * n), true);
+        gm_apply_flow<T>(M, L, U, D, vj, k.st, rs::APPLY_RUN, flow, s, ps);
+    } else if (fz) {
         const bool yin = y_from_input(M, sizeof(T) == sizeof(double), true);
         ProfScope ps(PC_APPLY, s, lower_bytes(M, sizeof(T), B) + upper_bytes(M, sizeof(T), B) + fb, false, true);
         lower_levels<T>(M, L, D, vj, k.phat, false, k, k.st, B, s, true, yin);
@@ -1863,7 +1898,7 @@ static void gm_step(ilu0_t M, const T *L, const T *U, const T *D, const rs::GmWo
     } else {
         apply_levels<T>(M, L, U, D, vj, k.phat, false, k, k.st, B, s);
     }
-    {
+    if (!flow.on) {
         ProfScope ps(PC_SPMV_T, s, B * (76 * nnzb + 4 * n + 48 * n) - fb, true);
         rs::launch_spmv_running(M->an->dev, M->pvals.as<double>(), (size_t)M->nnzb * 9, k.phat, k.t, k.vstride, k.st,
                                 B, M->spmv_variant, M->wdev, s, ps.start(), ps.stop(),
@@ -1893,7 +1928,7 @@ static void gm_step(ilu0_t M, const T *L, const T *U, const T *D, const rs::GmWo
 // End of a cycle: x += M^-1 (V y) for every system not done, then the
 // restart of those still iterating from r = P b - A x.
 template <typename T>
-static void gm_cycle_end(ilu0_t M, const T *L, const T *U, const T *D, const rs::GmWork &g, int cols,
+static void gm_cycle_end(ilu0_t M, const T *L, const T *U, const T *D, const rs::GmWork &g, int cols, GmFlow &flow,
                          hipStream_t s) {
     Krylov &k = M->k;
     const int B = M->batch;
@@ -1903,10 +1938,21 @@ static void gm_cycle_end(ilu0_t M, const T *L, const T *U, const T *D, const rs:
         ProfScope ps(PC_VEC, s, vb * (cols + 1), true);
         rs::launch_gm_combine(g, k.s, M->n, B, s, ps.start(), ps.stop());
     }
-    apply_levels<T>(M, L, U, D, k.s, k.phat, false, k, nullptr, B, s);
+    const double *z = k.phat;
+    if (flow.on) {
+        // both counters clear: the launch takes the second and so leaves the
+        // first clear, as the next cycle and the next solve find it
+        flow.pair = 0;
+        flow.ctr = 1;
+        rs::launch_flow_pair(k, M->n, B, s);
+        ProfScope ps(PC_APPLY, s, lower_bytes(M, sizeof(T), B) + upper_bytes(M, sizeof(T), B), true);
+        z = gm_apply_flow<T>(M, L, U, D, k.s, nullptr, rs::APPLY_ONLY, flow, s, ps);
+    } else {
+        apply_levels<T>(M, L, U, D, k.s, k.phat, false, k, nullptr, B, s);
+    }
     {
         ProfScope ps(PC_VEC, s, vb * 3, true);
-        rs::launch_gm_xupdate(g, k.x, k.phat, M->n, B, s, ps.start(), ps.stop());
+        rs::launch_gm_xupdate(g, k.x, z, M->n, B, s, ps.start(), ps.stop());
     }
     rs::launch_gm_phase(g, B, s);
     {
@@ -1924,18 +1970,18 @@ static void gm_cycle_end(ilu0_t M, const T *L, const T *U, const T *D, const rs:
     }
 }
 
-static void gm_step_any(ilu0_t M, const rs::GmWork &g, int j, hipStream_t s) {
+static void gm_step_any(ilu0_t M, const rs::GmWork &g, int j, GmFlow &flow, hipStream_t s) {
     if (M->precision == RS_PREC_FP32_FACTORS)
-        gm_step<float>(M, M->Lf.as<float>(), M->Uf.as<float>(), M->Dinvf.as<float>(), g, j, s);
+        gm_step<float>(M, M->Lf.as<float>(), M->Uf.as<float>(), M->Dinvf.as<float>(), g, j, flow, s);
     else
-        gm_step<double>(M, M->L.as<double>(), M->U.as<double>(), M->Dinv.as<double>(), g, j, s);
+        gm_step<double>(M, M->L.as<double>(), M->U.as<double>(), M->Dinv.as<double>(), g, j, flow, s);
 }
 
-static void gm_cycle_end_any(ilu0_t M, const rs::GmWork &g, int cols, hipStream_t s) {
+static void gm_cycle_end_any(ilu0_t M, const rs::GmWork &g, int cols, GmFlow &flow, hipStream_t s) {
     if (M->precision == RS_PREC_FP32_FACTORS)
-        gm_cycle_end<float>(M, M->Lf.as<float>(), M->Uf.as<float>(), M->Dinvf.as<float>(), g, cols, s);
+        gm_cycle_end<float>(M, M->Lf.as<float>(), M->Uf.as<float>(), M->Dinvf.as<float>(), g, cols, flow, s);
     else
-        gm_cycle_end<double>(M, M->L.as<double>(), M->U.as<double>(), M->Dinv.as<double>(), g, cols, s);
+        gm_cycle_end<double>(M, M->L.as<double>(), M->U.as<double>(), M->Dinv.as<double>(), g, cols, flow, s);
 }
 
 extern "C" {
@@ -1959,7 +2005,13 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
     if (st != RS_OK) return st;
     st = ensure_wells(M, A, s);
     if (st != RS_OK) return st;
-    if (reads_u(M, false) && (st = ensure_u(M, s)) != RS_OK) return st;
+    GmFlow flow;
+    flow.on = flow_size(M);
+    if (flow.on) {
+        if ((st = ensure_flow(M, s)) != RS_OK) return st;
+    } else if (reads_u(M, false) && (st = ensure_u(M, s)) != RS_OK) {
+        return st;
+    }
     Krylov &k = M->k;
     // basis: restart columns (the column a cycle's last step would add is
     // never used); zeroed once, so the padding of every column stays zero
@@ -1994,7 +2046,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         // r = rhat = P b, x = 0, ||b||, the initial tests; the first cycle
         // starts from v_0 = r / ||b||
         ProfScope ps(PC_VEC, s, (double)B * 152 * M->n);
-        rs::launch_setup(M->an->dev, bd, M->bad.as<int32_t>(), reduction, max_iter, k, B, false, s);
+        rs::launch_setup(M->an->dev, bd, M->bad.as<int32_t>(), reduction, max_iter, k, B, flow.on, s);
     }
     rs::launch_gm_init(g, B, s);
     rs::launch_gm_normalise(g, k.r, 0, 0, M->n, B, s);
@@ -2017,8 +2069,8 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipEventRecord(M->ev_s1, s));
         HIP_TRY(hipMemcpyAsync(M->h_state, k.st, B * sizeof(SysState), hipMemcpyDeviceToHost, s));
-        // only single-launch sweeps touch the sweep counters
-        if (M->tile_sweeps) HIP_TRY(hipMemcpyAsync(M->h_ctr, k.lctr, 2 * sizeof(rs::SweepCtr), hipMemcpyDeviceToHost, s));
+        // only single-launch sweeps and applications touch the counters
+        if (M->tile_sweeps || flow.on) HIP_TRY(hipMemcpyAsync(M->h_ctr, k.lctr, 2 * sizeof(rs::SweepCtr), hipMemcpyDeviceToHost, s));
         if (mem != RS_MEM_DEVICE) HIP_TRY(hipMemcpyAsync(x, xd, m * sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         return RS_OK;
@@ -2044,7 +2096,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         int cols = 0;
         bool stopped = false;
         for (int j = 0; j < restart; ++j) {
-            gm_step_any(M, g, j, s);
+            gm_step_any(M, g, j, flow, s);
             ++queued;
             cols = j + 1;
             if (j + 1 == restart) break;
@@ -2060,7 +2112,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
             ProfScope ps(PC_VEC, s, (double)B * 48 * M->n, true);
             rs::launch_gm_normalise(g, k.t, j + 1, 1, M->n, B, s, ps.start(), ps.stop());
         }
-        gm_cycle_end_any(M, g, cols, s);
+        gm_cycle_end_any(M, g, cols, flow, s);
         HIP_TRY(hipGetLastError());
         if (stopped) {
             st = finish();
@@ -2078,7 +2130,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         st = finish();
         if (st != RS_OK) return st;
     }
-    if (M->tile_sweeps && (M->h_ctr[0].error || M->h_ctr[1].error)) return sweep_reset(M, s);
+    if ((M->tile_sweeps || flow.on) && (M->h_ctr[0].error || M->h_ctr[1].error)) return sweep_reset(M, s);
     const double solve_ms = elapsed_ms(M->ev_s0, M->ev_s1);
     int worst = RS_OK, needed = 1;
     for (int i = 0; i < B; ++i) {

@@ -290,6 +290,8 @@ void launch_apply_flow(const DevSchedule &d, const T *L, const T *U, const T *Di
                        Krylov &k, SysState *st, SweepCtr *ctr, SweepCtr *next, int u0_end, int nsys, int mode,
                        bool fused, bool lp, int spmv_variant, int levels, int grid, int spin, hipStream_t s,
                        hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// Mark y (whole) and phat (its n rows) for a launch_apply_flow, clear both counters.
+void launch_flow_pair(Krylov &k, int n, int nsys, hipStream_t s);
 // t2 = D^-1 (B x) for every well and system (x at stride xstride): the
 // first half of the separate well application, run before an SpMV of x.
 void launch_wells_t2(const WellsDev &w, const double *x, size_t xstride, int nsys, hipStream_t s);

@@ -2267,6 +2267,20 @@ __global__ void __launch_bounds__(kTotalThreads) k_spmv_total(double *__restrict
 // grid-strided.  Vectors are padded to whole tiles with zeros, so there are
 // no bounds checks (the padding contributes zeros to every reduction).
 
+// y (whole, of either factor type) and phat (but for its padding of zeros)
+// marked for k_apply_flow, both counters clear.
+__global__ void __launch_bounds__(kVecThreads) k_flow_pair(int n, Krylov k) {
+    if (blockIdx.y == 0) {
+        flow_clear(k.lctr);
+        flow_clear(k.uctr);
+    }
+    const size_t vo = (size_t)blockIdx.y * k.vstride;
+    for (size_t e = (size_t)blockIdx.x * kVecThreads + threadIdx.x; e < k.vstride; e += (size_t)gridDim.x * kVecThreads) {
+        flow_mark((double *)k.y + vo + e);
+        if (e < 3 * (size_t)n) flow_mark(k.phat + vo + e);
+    }
+}
+
 // r = rhat = P b, x = p = v = 0 (padding included), ||b||; initial scalars.
 __global__ void __launch_bounds__(kVecThreads) k_setup(int n, const int32_t *__restrict__ perm,
                                                        const double *__restrict__ b, Krylov k,
@@ -3059,6 +3073,11 @@ void launch_setup(const DevSchedule &d, const double *b_orig, const int32_t *bad
                   Krylov &k, int nsys, bool flow, hipStream_t s) {
     k_setup<<<dim3(vec_blocks(d.n), nsys), kVecThreads, 0, s>>>(d.n, d.perm, b_orig, k, bad, reduction, max_iter,
                                                                 flow ? 1 : 0);
+}
+
+void launch_flow_pair(Krylov &k, int n, int nsys, hipStream_t s) {
+    if (n <= 0 || nsys <= 0) return;
+    k_flow_pair<<<dim3(copy_blocks(k.vstride), nsys), kVecThreads, 0, s>>>(n, k);
 }
 
 void launch_spmv_v(const DevSchedule &d, const double *Ap, size_t a_stride, Krylov &k, int nsys, int variant,

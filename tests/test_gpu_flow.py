@@ -198,3 +198,28 @@ def test_polled_reduction_adds_every_partial(n):
         norms = [s.solve(b, reduction=0.0, max_iter=0)[2][0]["r0_norm"] for _ in range(2)]
     want = np.linalg.norm(b)
     assert norms[0] == norms[1] and abs(norms[0] - want) <= 3 * n * np.finfo(np.float64).eps * want
+
+
+@pytest.mark.parametrize("precision", [rs.PREC_FP64, rs.PREC_FP32_FACTORS])
+@pytest.mark.parametrize("restart", [3, 30])
+@pytest.mark.parametrize("name", ["chain_257", "dense_40", "grid16x8x8", "grid23x17x15", "nnc", "big_nnc", "ensemble"])
+def test_gmres_with_applications_in_one_launch(name, restart, precision):
+    """GMRES on a small system against the separate launches (graphs off): the
+    same bits, over restarts and with systems of a batch that stop apart."""
+    if name == "big_nnc":
+        s = make_grid_system(31, 23, 12, active_frac=0.9, nnc_frac=0.03, seed=6)
+        rowptr, colidx, vals = s.rowptr, s.colidx, s.vals
+    else:
+        rowptr, colidx, vals = _pattern(name)
+    n, batch = len(rowptr) - 1, vals.shape[0]
+    b = np.random.default_rng(9).standard_normal((batch, n, 3))
+    b[0] *= np.linspace(1.0, 1e4, n)[:, None]
+    with rs.Solver(rowptr, colidx, vals, ordering=rs.ORDER_GRAPH_COLOUR, precision=precision) as s:
+        s.factor()
+        got = []
+        for graph in (0, 1, 1):
+            rs.ilu0_set_option(s.M, rs.OPT_USE_GRAPH, graph)
+            x, st, info = s.solve_gmres(b, restart=restart, reduction=1e-5, max_iter=60)
+            got.append((x, st, [(i["status"], i["half_steps"], i["final_norm"], i["true_rel_residual"]) for i in info]))
+    for g in got[1:]:
+        assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:]
