@@ -110,8 +110,10 @@ enum rs_option {
                                 end without converging leave the prediction unchanged */
     RS_OPT_SPMV_VARIANT = 5, /* launch shape of the SpMVs: 0..8 = {4, 2, 1} waves per workgroup
                                 with blocks staged in LDS, then the same three reading directly,
-                                then the same three staged in LDS with non-temporal loads */
-    RS_OPT_SWEEP_VARIANT = 6, /* launch shape of the one-launch-per-level sweeps (same encoding) */
+                                then the same three staged in LDS with non-temporal loads
+                                (default 0, from 10 000 rows on 2, from 250 000 on 8) */
+    RS_OPT_SWEEP_VARIANT = 6, /* launch shape of the one-launch-per-level sweeps (same encoding;
+                                default 2, from 250 000 rows on 8) */
     RS_OPT_REDUCE_SPLIT = 7, /* dot products fused into the SpMVs: 0 (default) = each workgroup
                                 joins a ticket tree inside the SpMV; 1 = each wave only stores
                                 its partial and a one-workgroup kernel adds them; 2 = each wave

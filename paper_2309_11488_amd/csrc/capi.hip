@@ -396,6 +396,7 @@ int bcsr_create(int32_t n_brows, int32_t nnzb, int32_t block_size, int32_t batch
     A->n = n_brows;
     A->nnzb = nnzb;
     A->batch = batch;
+    A->spmv_variant = rs::default_spmv_variant(n_brows);
     int st = read_pattern(n_brows, nnzb, row_ptr, col_idx, mem, (hipStream_t)stream, A->h_rowptr, A->h_colidx);
     if (st != RS_OK) { delete A; return st; }
     int bad = -1;
@@ -606,6 +607,8 @@ static rs_ilu0 *new_ilu0(const rs_bcsr *A, std::shared_ptr<const Analysis> an) {
     M->nnzb = A->nnzb;
     M->batch = A->batch;
     M->hash = A->hash;
+    M->spmv_variant = rs::default_spmv_variant(M->n);
+    M->sweep_variant = rs::default_sweep_variant(M->n);
     // many thin levels (natural order, level sets): one launch per sweep;
     // few wide colours or levels (colouring, RCM then level sets): one
     // launch per colour or level

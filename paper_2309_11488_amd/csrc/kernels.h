@@ -134,6 +134,17 @@ inline int row_blocks(int rows, int waves = kWavesPerBlock) {
 // every shape.
 enum RowVariant { RV_W4_LDS = 0, RV_W2_LDS = 1, RV_W1_LDS = 2, RV_W4_DIRECT = 3, RV_W2_DIRECT = 4, RV_W1_DIRECT = 5,
                   RV_W4_LDS_NT = 6, RV_W2_LDS_NT = 7, RV_W1_LDS_NT = 8, RV_COUNT = 9 };
+// The shapes a handle of n rows starts with.  One wave a workgroup (no
+// barrier between the waves of a larger one) is never slower: 50 000 cells
+// 246 against 258 us a solve, 64 systems of 48 000 cells 3.76 against 3.95
+// ms.  Non-temporal loads of the blocks pay once the vectors outgrow the L2s:
+// 280k cells with NNCs 700 against 757 us, 1M cells 2.24 against 2.39 ms, but
+// 120k cells 333 against 319.  By the rows of one system, so that a system
+// has the same partials alone and in a batch; the SpMVs of less than 10 000
+// rows, whose solves spend their time on launches, keep the partials of four
+// waves.
+inline int default_sweep_variant(int n) { return n >= 250000 ? RV_W1_LDS_NT : RV_W1_LDS; }
+inline int default_spmv_variant(int n) { return n >= 10000 ? default_sweep_variant(n) : RV_W4_LDS; }
 inline int variant_waves(int v) { return v % 3 == 0 ? 4 : (v % 3 == 1 ? 2 : 1); }
 // SpMV workgroups: one row tile each.
 inline int spmv_grid(int n, int waves) { return std::max(1, row_blocks(n, waves)); }
