@@ -356,7 +356,11 @@ int ilu0_factor_status(ilu0_t M, int32_t *bad_row);
 int ilu0_get_factors(ilu0_t M, int32_t sys, double *lu, double *dinv);
 
 /* ilu0_apply -- z = U^{-1} L^{-1} v for systems [first_sys, first_sys +
- * n_sys) in caller order (equations 3-4).  Stream-ordered. */
+ * n_sys) in caller order (equations 3-4).  Stream-ordered: with device
+ * vectors and per-level sweeps the call returns when its work is queued (v
+ * and z must stay valid until `stream` has passed it; the handle's later
+ * calls, on any stream, come after it).  With host vectors or single-launch
+ * sweeps (RS_OPT_SWEEP_TILES) it synchronises `stream`.  Not to be captured. */
 int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t n_sys, int32_t mem,
                void *stream);
 

@@ -223,3 +223,32 @@ def test_gmres_with_applications_in_one_launch(name, restart, precision):
             got.append((x, st, [(i["status"], i["half_steps"], i["final_norm"], i["true_rel_residual"]) for i in info]))
     for g in got[1:]:
         assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:]
+
+
+@pytest.mark.parametrize("tiles", [0, 1])
+def test_queued_applications_keep_the_handle_in_order_across_streams(tiles):
+    """A device caller's application returns before its work is done; the
+    handle's next call works in the same buffers, on whatever stream."""
+    torch = pytest.importorskip("torch")
+    s = make_grid_system(37, 31, 23, seed=8)
+    rng = np.random.default_rng(2)
+    v = torch.from_numpy(rng.standard_normal((6, s.n, 3))).cuda()
+    with rs.Solver(s.rowptr, s.colidx, s.vals, ordering=rs.ORDER_GRAPH_COLOUR) as sol:
+        rs.ilu0_set_option(sol.M, rs.OPT_SWEEP_TILES, tiles)
+        sol.factor()
+        want = [rs.ilu0_apply(sol.M, v[k].cpu().numpy()[None]) for k in range(6)]
+        xw, st, _ = sol.solve(s.b[:, 0])
+        assert st == rs.OK
+        b = torch.from_numpy(np.ascontiguousarray(s.b[:, 0])).cuda()
+        z, x = torch.empty_like(v), torch.empty_like(b)
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        torch.cuda.synchronize()
+        for rep in range(3):
+            z.zero_()
+            torch.cuda.synchronize()
+            for k in range(6):
+                rs.ilu0_apply(sol.M, v[k], z[k], stream=streams[(k + rep) % 3].cuda_stream)
+            rs.bicgstab_solve(sol.M, sol.A, b, x, stream=streams[(rep + 1) % 3].cuda_stream)
+            torch.cuda.synchronize()
+            assert all(np.array_equal(z[k].cpu().numpy(), want[k][0]) for k in range(6))
+            assert np.array_equal(x.cpu().numpy(), xw)
