@@ -252,3 +252,23 @@ def test_queued_applications_keep_the_handle_in_order_across_streams(tiles):
             torch.cuda.synchronize()
             assert all(np.array_equal(z[k].cpu().numpy(), want[k][0]) for k in range(6))
             assert np.array_equal(x.cpu().numpy(), xw)
+
+
+@pytest.mark.parametrize("precision", [rs.PREC_FP64, rs.PREC_FP32_FACTORS])
+@pytest.mark.parametrize("batch", [64, 65])
+def test_streamed_factor_stores_equal_the_cached_ones(batch, precision):
+    """250 000 rows of all systems and more write their factors with
+    non-temporal stores: the member's factors alone, bit for bit."""
+    s = make_grid_system(21, 17, 11, seed=12)      # 3 927 rows: 251 328 and 255 255
+    scale = 1.0 + np.arange(batch) / 64.0
+    nnzb = len(s.colidx)
+    with rs.Solver(s.rowptr, s.colidx, s.vals[0] * scale[:, None, None, None], ordering=rs.ORDER_GRAPH_COLOUR,
+                   precision=precision) as many:
+        many.factor()
+        for k in (0, 1, batch - 1):
+            got = rs.ilu0_get_factors(many.M, k, s.n, nnzb)
+            with rs.Solver(s.rowptr, s.colidx, s.vals * scale[k], ordering=rs.ORDER_GRAPH_COLOUR,
+                           precision=precision) as one:
+                one.factor()
+                want = rs.ilu0_get_factors(one.M, 0, s.n, nnzb)
+            assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
