@@ -541,6 +541,12 @@ int build_schedule(int n, int nnzb, const int32_t *rowptr, const int32_t *colidx
         s.y_in = ok ? 1 : 0;
     }
 
+    if (s.nu_levels > 0) {
+        std::vector<char> last(n, 0);
+        for (int q = 0; q < s.uset[1]; ++q) last[s.urows[q]] = 1;
+        for (size_t e = 0; e < s.lcol.size() && !s.y_last; ++e) s.y_last = last[s.lcol[e]];
+    }
+
     s.lnarrow.assign(s.nl_levels, 1);
     for (int l = 0; l < s.nl_levels; ++l)
         for (int q = s.lset[l]; q < s.lset[l + 1]; ++q) {

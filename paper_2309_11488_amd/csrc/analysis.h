@@ -80,6 +80,10 @@ struct Schedule {
     // fuse_n0 sits at L-schedule position i and U-schedule position
     // i - fuse_n0.
     int y_in = 0;
+    // y_last = 1: some row's L names a row without upper blocks (a structurally
+    // non-symmetric pattern), so the lower launches store that row's y too
+    // although they finish it.
+    int y_last = 0;
     // row tiles of the single-launch sweeps: tile t covers schedule
     // positions [ltiles[t], ltiles[t+1]) inside one level
     std::vector<int32_t> ltiles, utiles;

@@ -592,7 +592,7 @@ static int build_analysis(const rs_bcsr *A, int32_t ordering, const int32_t *par
     d.lsrc_a = an->lsrc_a.as<int32_t>(); d.usrc_a = an->usrc_a.as<int32_t>(); d.dsrc_a = an->dsrc_a.as<int32_t>();
     d.nrest = (int)S.rest_dst.size();
     d.rest_dst = an->rest_dst.as<int32_t>(); d.rest_src = an->rest_src.as<int32_t>();
-    d.fuse_n0 = S.fuse_n0; d.fuse_q0 = S.fuse_q0;
+    d.fuse_n0 = S.fuse_n0; d.fuse_q0 = S.fuse_q0; d.y_last = S.y_last;
     d.nlt = (int)S.ltiles.size() - 1; d.nut = (int)S.utiles.size() - 1;
     d.lt_start = an->lt_start.as<int32_t>(); d.ut_start = an->ut_start.as<int32_t>();
     auto tiles = [](const rs::Schedule::ApplyTiles &t, const DevBuf &lt, const DevBuf &ut) {

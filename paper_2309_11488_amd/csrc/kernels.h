@@ -34,6 +34,7 @@ struct DevSchedule {
     // rows 0 .. fuse_n0 hold no lower blocks and sit at U-schedule
     // positions fuse_q0 + i of one upper level (0: no such rows)
     int fuse_n0, fuse_q0;
+    int y_last;   // rows without upper blocks keep their y (Schedule::y_last)
     // sweep tiles (see Schedule::Tiles)
     int nlt, nut;
     const int32_t *lt_start, *ut_start;

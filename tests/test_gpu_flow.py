@@ -272,3 +272,38 @@ def test_streamed_factor_stores_equal_the_cached_ones(batch, precision):
                 one.factor()
                 want = rs.ilu0_get_factors(one.M, 0, s.n, nnzb)
             assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("ordering", [rs.ORDER_LEVEL_SET, rs.ORDER_GRAPH_COLOUR, rs.ORDER_RCM_LEVEL_SET])
+@pytest.mark.parametrize("n", [3, 40, 600])
+def test_patterns_without_the_transposed_blocks(n, ordering):
+    """A row without upper blocks that a later row's L names: its y counts in
+    every form of the sweeps."""
+    rng = np.random.default_rng(n)
+    mask = np.eye(n, dtype=bool)
+    mask[1 + np.arange(n - 1), np.arange(n - 1) // 2] = True      # blocks below the diagonal only
+    mask[rng.integers(0, n, n // 3), rng.integers(0, n, n // 3)] = True
+    rowptr = np.concatenate([[0], np.cumsum(mask.sum(1))]).astype(np.int32)
+    rows, cols = np.nonzero(mask)
+    vals = rng.uniform(-1, 1, (1, len(cols), 3, 3)) / 4.0
+    vals[0, rows == cols] += 6.0 * np.eye(3)
+    v = rng.standard_normal((1, n, 3))
+    with rs.Solver(rowptr, cols.astype(np.int32), vals, ordering=ordering) as s:
+        s.factor()
+        perm, _, _ = rs.ilu0_get_schedule(s.M, n)
+        prow, pcol, pv = oracle.permute(rowptr, cols.astype(np.int32), vals[0], perm)
+        st, _, lu, dinv = oracle.ilu0(prow, pcol, pv)
+        want = np.empty((n, 3))
+        want[perm] = oracle.apply(prow, pcol, lu, dinv, v[0][perm])
+        for tiles in (0, 1):
+            rs.ilu0_set_option(s.M, rs.OPT_SWEEP_TILES, tiles)
+            z = rs.ilu0_apply(s.M, v)
+            assert np.linalg.norm(z[0] - want) <= 1e-12 * np.linalg.norm(want)
+        rs.ilu0_set_option(s.M, rs.OPT_SWEEP_TILES, 0)
+        got = []
+        for graph in (0, 1):
+            rs.ilu0_set_option(s.M, rs.OPT_USE_GRAPH, graph)
+            x, st, info = s.solve(v, reduction=1e-6)
+            assert st == rs.OK
+            got.append((x, info[0]["half_steps"]))
+    assert np.array_equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
