@@ -400,7 +400,7 @@ int bcsr_create(int32_t n_brows, int32_t nnzb, int32_t block_size, int32_t batch
     A->n = n_brows;
     A->nnzb = nnzb;
     A->batch = batch;
-    A->spmv_variant = rs::default_spmv_variant(n_brows);
+    A->spmv_variant = rs::default_sweep_variant(n_brows);   // no dot products: as a sweep
     int st = read_pattern(n_brows, nnzb, row_ptr, col_idx, mem, (hipStream_t)stream, A->h_rowptr, A->h_colidx);
     if (st != RS_OK) { delete A; return st; }
     int bad = -1;
@@ -611,7 +611,7 @@ static rs_ilu0 *new_ilu0(const rs_bcsr *A, std::shared_ptr<const Analysis> an) {
     M->nnzb = A->nnzb;
     M->batch = A->batch;
     M->hash = A->hash;
-    M->spmv_variant = rs::default_spmv_variant(M->n);
+    M->spmv_variant = rs::default_spmv_variant(M->n, M->batch);
     M->sweep_variant = rs::default_sweep_variant(M->n);
     // many thin levels (natural order, level sets): one launch per sweep;
     // few wide colours or levels (colouring, RCM then level sets): one

@@ -135,17 +135,22 @@ inline int row_blocks(int rows, int waves = kWavesPerBlock) {
 // every shape.
 enum RowVariant { RV_W4_LDS = 0, RV_W2_LDS = 1, RV_W1_LDS = 2, RV_W4_DIRECT = 3, RV_W2_DIRECT = 4, RV_W1_DIRECT = 5,
                   RV_W4_LDS_NT = 6, RV_W2_LDS_NT = 7, RV_W1_LDS_NT = 8, RV_COUNT = 9 };
-// The shapes a handle of n rows starts with.  One wave a workgroup (no
-// barrier between the waves of a larger one) is never slower: 50 000 cells
-// 246 against 258 us a solve, 64 systems of 48 000 cells 3.76 against 3.95
-// ms.  Non-temporal loads of the blocks pay once the vectors outgrow the L2s:
-// 280k cells with NNCs 700 against 757 us, 1M cells 2.24 against 2.39 ms, but
-// 120k cells 333 against 319.  By the rows of one system, so that a system
-// has the same partials alone and in a batch; the SpMVs of less than 10 000
-// rows, whose solves spend their time on launches, keep the partials of four
-// waves.
+// The shapes a handle of n rows (a system) starts with.  Sweeps take one wave
+// a workgroup: there is no barrier between the waves of a larger one.
+// Non-temporal loads of the blocks pay once the vectors outgrow the L2s: 280k
+// cells with NNCs 700 against 757 us a solve, 1M cells 2.24 against 2.39 ms,
+// but 120k cells 333 against 319.  Products take one wave from 250 000 rows of
+// all systems on (a step of 1M cells 3.00 against 3.02 ms, of 64 systems of
+// 48 000 cells 5.64 against 5.76); below, their workgroups are few and the
+// tickets of their partials weigh more (50 000 cells with wells 385 against
+// 398 us).  The partials are those of four waves either way (sum_per): another
+// order changes the last bits of alpha and omega, which an ill-conditioned
+// system (one in a dozen of 50 000 cells with strong wells) carries into
+// digits of x.
 inline int default_sweep_variant(int n) { return n >= 250000 ? RV_W1_LDS_NT : RV_W1_LDS; }
-inline int default_spmv_variant(int n) { return n >= 10000 ? default_sweep_variant(n) : RV_W4_LDS; }
+inline int default_spmv_variant(int n, int batch) {
+    return (double)n * batch >= 250000.0 ? default_sweep_variant(n) : RV_W4_LDS;
+}
 inline int variant_waves(int v) { return v % 3 == 0 ? 4 : (v % 3 == 1 ? 2 : 1); }
 // SpMV workgroups: one row tile each.
 inline int spmv_grid(int n, int waves) { return std::max(1, row_blocks(n, waves)); }
@@ -162,11 +167,16 @@ constexpr int kTotalThreads = 1024;   // threads of the one-workgroup summing ke
 struct SpmvSums {
     int offset, count;
 };
+// Workgroups whose sums make one partial of the tree (group_reduce), 32 of
+// which make a group: a product of one-wave workgroups has the bits of one of
+// four waves.
+constexpr int sum_per(int waves) { return waves == 1 ? 4 : 1; }
+inline int sum_groups(int blocks, int waves) { return (blocks + 32 * sum_per(waves) - 1) / (32 * sum_per(waves)); }
 inline SpmvSums spmv_sums(int n, int waves, int split) {
     const int g = spmv_grid(n, waves);
     if (split == 1) return SpmvSums{2 * g * waves, 1};       // k_spmv_total's sum after the wave partials
     if (split == 2) return SpmvSums{0, g * waves};           // the wave partials themselves
-    return SpmvSums{2 * g, (g + 31) / 32};                   // the ticket tree's group sums
+    return SpmvSums{2 * g, sum_groups(g, waves)};            // the ticket tree's group sums
 }
 // Reduction scratch of a system whose largest launch has `blocks` workgroups.
 inline size_t part_stride_for(int blocks) { return 2 * (size_t)blocks + 2 * ((size_t)blocks / 32 + 1) + 16; }

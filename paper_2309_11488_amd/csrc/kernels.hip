@@ -83,13 +83,14 @@ __device__ inline void block_sum(double (&v)[NV], double *lds) {
 // group g (one 128-byte line per counter, so groups do not contend).
 constexpr int kGroup = 32;
 
-template <int NV>
+template <int NV, int PER = 1>
 __device__ bool grid_reduce(double (&v)[NV], double *part, uint32_t *tickets, int nblk, int bx) {
     __shared__ double lds[16 * NV];
     __shared__ int glast, last;
     block_sum<NV>(v, lds);
-    const int ng = (nblk + kGroup - 1) / kGroup, g = bx / kGroup;
-    const int gsize = min(kGroup, nblk - g * kGroup);
+    constexpr int size = kGroup * PER;   // (see group_reduce)
+    const int ng = (nblk + size - 1) / size, g = bx / size;
+    const int gsize = min(size, nblk - g * size);
     double *gpart = part + (size_t)nblk * NV;
     if (threadIdx.x == 0) {
         for (int k = 0; k < NV; ++k)
@@ -108,9 +109,12 @@ __device__ bool grid_reduce(double (&v)[NV], double *part, uint32_t *tickets, in
             const int lane = threadIdx.x;
             double gs[NV];
             for (int k = 0; k < NV; ++k) {
-                const double p = lane < gsize ? __hip_atomic_load(part + (size_t)(g * kGroup + lane) * NV + k,
-                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                              : 0.0;
+                double p = 0.0;
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    if (lane < kGroup && lane * PER + i < gsize)
+                        p += __hip_atomic_load(part + (size_t)(g * size + lane * PER + i) * NV + k, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
                 gs[k] = wave_sum(p);
             }
             if (lane == 0) {
@@ -154,14 +158,17 @@ __device__ bool grid_reduce(double (&v)[NV], double *part, uint32_t *tickets, in
 }
 
 // First level of grid_reduce only: the last workgroup of each group of
-// kGroup stores the group's sum at part[nblk*NV + g*NV].  A later kernel adds
-// the ceil(nblk / kGroup) group sums (no top-level counter, no serial tail).
-template <int NV>
+// kGroup PER stores the group's sum at part[nblk*NV + g*NV].  A later kernel adds
+// the group sums (no top-level counter, no serial tail).  PER workgroups make a
+// partial: one-wave workgroups take sum_per(1) = 4, added in order, which
+// gives the bits of four-wave workgroups.
+template <int NV, int PER>
 __device__ void group_reduce(double (&v)[NV], double *part, uint32_t *tickets, int nblk, int bx) {
     __shared__ double lds[16 * NV];
     __shared__ int glast;
     block_sum<NV>(v, lds);
-    const int g = bx / kGroup, gsize = min(kGroup, nblk - g * kGroup);
+    constexpr int size = kGroup * PER;
+    const int g = bx / size, gsize = min(size, nblk - g * size);
     if (threadIdx.x == 0) {
         for (int k = 0; k < NV; ++k)
             __hip_atomic_store(part + (size_t)bx * NV + k, v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -176,9 +183,12 @@ __device__ void group_reduce(double (&v)[NV], double *part, uint32_t *tickets, i
         const int lane = threadIdx.x;
         double gs[NV];
         for (int k = 0; k < NV; ++k) {
-            const double p = lane < gsize ? __hip_atomic_load(part + (size_t)(g * kGroup + lane) * NV + k,
-                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                          : 0.0;
+            double p = 0.0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (lane < kGroup && lane * PER + i < gsize)
+                    p += __hip_atomic_load(part + (size_t)(g * size + lane * PER + i) * NV + k, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
             gs[k] = wave_sum(p);
         }
         if (lane == 0) {
@@ -1578,8 +1588,8 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kRo
     if (MODE == SPMV_V || MODE == SPMV_T) {
         // group sums of (rhat, v) or of (t, s) and (t, t); the next kernel
         // adds the group sums (kernel boundary: no serial tail here)
-        group_reduce<2>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx);
-    } else if (grid_reduce<2>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx) &&
+        group_reduce<2, sum_per(W)>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx);
+    } else if (grid_reduce<2, sum_per(W)>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx) &&
                threadIdx.x == 0) {
         st[sys].true_res = v[1] > 0.0 ? sqrt(v[0]) / sqrt(v[1]) : 0.0;
     }
@@ -1635,8 +1645,8 @@ struct ApplyArgs {
 
 // The sums of a tile's dot products as the row kernels leave them: sv holds
 // the terms of each row component, virtual wave w adds rows [21 w, 21 w + 21)
-// of the tile, vw of them make a workgroup's partial, 32 partials a group
-// sum (group_reduce).  Called by the whole workgroup.
+// of the tile, vw of them make a workgroup's partial, 32 sum_per(vw) partials
+// a group sum (group_reduce).  Called by the whole workgroup.
 template <int R>
 __device__ inline void apply_sums(const double (&sv)[2][3 * R], int tile, int vw, int nblk, double *part,
                                   uint32_t *tickets) {
@@ -1652,7 +1662,8 @@ __device__ inline void apply_sums(const double (&sv)[2][3 * R], int tile, int vw
     __syncthreads();
     const int bx = tile * (NW / vw) + w;
     if (w >= NW / vw || bx >= nblk) return;
-    const int g = bx / kGroup, gsize = min(kGroup, nblk - g * kGroup);
+    const int per = sum_per(vw), size = kGroup * per;
+    const int g = bx / size, gsize = min(size, nblk - g * size);
     uint32_t t = 0;
     if (lane == 0) {
         for (int k = 0; k < 2; ++k) {
@@ -1668,10 +1679,14 @@ __device__ inline void apply_sums(const double (&sv)[2][3 * R], int tile, int vw
     }
     if (__builtin_amdgcn_readfirstlane(t) != (uint32_t)(gsize - 1)) return;
     double gs[2];
-    for (int k = 0; k < 2; ++k)
-        gs[k] = wave_sum(lane < gsize ? __hip_atomic_load(part + (size_t)(g * kGroup + lane) * 2 + k, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT)
-                                      : 0.0);
+    for (int k = 0; k < 2; ++k) {
+        double p = 0.0;
+        for (int i = 0; i < per; ++i)
+            if (lane < kGroup && lane * per + i < gsize)
+                p += __hip_atomic_load(part + (size_t)(g * size + lane * per + i) * 2 + k, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        gs[k] = wave_sum(p);
+    }
     if (lane == 0) {
         __hip_atomic_store(tickets + (size_t)kTicketPad * (1 + g), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int k = 0; k < 2; ++k) part[(size_t)nblk * 2 + (size_t)g * 2 + k] = gs[k];
@@ -2047,7 +2062,7 @@ k_usweep_spmv(DevSchedule d, const double *__restrict__ Ap, size_t a_stride, con
         v[0] = w * av;
         v[1] = av * av;
     }
-    group_reduce<2>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx);
+    group_reduce<2, sum_per(W)>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx);
 }
 
 // v = A phat on the rows [r0, n) (the rows with lower blocks of a two-level
@@ -2129,7 +2144,7 @@ k_spmv_lp(int n, int r0, const int32_t *__restrict__ ptr, const int32_t *__restr
         v[0] = w * acc;
         v[1] = acc * acc;
     }
-    group_reduce<2>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx);
+    group_reduce<2, sum_per(W)>(v, part + sys * part_stride, tk + sys * tk_stride, gridDim.x, bx);
 }
 
 // The second preconditioner application's lower launch for the rows
@@ -2221,9 +2236,9 @@ __device__ inline void sum_products(const double *__restrict__ p, int np, const 
 // Deterministic grid reduction of the vector kernels: true in the last
 // workgroup, where thread 0's v[] holds the grid's total.  Every workgroup
 // stores its partial where it holds the mark (k_lsweep_flow) and ends; the
-// last one polls all partials, adds them (thread-strided, then the block
-// tree: the order depends on nblk alone) and marks them again.  A store and
-// a load, where the ticket tree of grid_reduce takes a store, its
+// last one polls all partials, adds them in the order of grid_reduce (groups
+// of kGroup by butterfly, then the group sums: the same bits) and marks them
+// again.  A store and a load, where the ticket tree takes a store, its
 // acknowledgement and an atomic on each of two levels.  No other
 // workgroup waits, so the polls end whatever the number of resident
 // workgroups; they are bounded all the same (a partial left marked is a
@@ -2236,8 +2251,7 @@ __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx) {
     if (threadIdx.x == 0)
         for (int k = 0; k < NV; ++k) flow_store<false>(part + (size_t)bx * NV + k, v[k]);
     if (bx != nblk - 1) return false;
-    double acc[NV];
-    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+    __shared__ double gsum[kVecMaxBlocks / kGroup][NV];
     constexpr int U = NV <= 4 ? 4 : 1;
     for (int b0 = 0; b0 < nblk; b0 += U * (int)blockDim.x) {
         uint64_t t[U][NV];
@@ -2254,15 +2268,27 @@ __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx) {
             if (!__any(miss)) break;
             asm volatile("" ::: "memory");
         }
+        // kGroup = 32 consecutive partials sit in one half of a wave
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (b0 + u * (int)blockDim.x + (int)threadIdx.x < nblk)
-                for (int k = 0; k < NV; ++k) acc[k] += __builtin_bit_cast(double, t[u][k]);
+        for (int u = 0; u < U; ++u) {
+            if (b0 + u * (int)blockDim.x >= nblk) break;
+            const int b = b0 + u * (int)blockDim.x + (int)threadIdx.x;
+            for (int k = 0; k < NV; ++k) {
+                double s = b < nblk ? __builtin_bit_cast(double, t[u][k]) : 0.0;
+                for (int o = kGroup / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+                if (b < nblk && b % kGroup == 0) gsum[b / kGroup][k] = s;
+            }
+        }
     }
-    block_sum<NV>(acc, lds);   // every thread has read its partials
+    __syncthreads();   // every thread has read its partials
     for (int e = threadIdx.x; e < nblk * NV; e += blockDim.x) flow_mark(part + e);
-    if (threadIdx.x == 0)
-        for (int k = 0; k < NV; ++k) v[k] = acc[k];
+    if (threadIdx.x < 64) {
+        const int ng = (nblk + kGroup - 1) / kGroup;
+        for (int k = 0; k < NV; ++k) {
+            const double s = wave_sum((int)threadIdx.x < ng ? gsum[threadIdx.x][k] : 0.0);
+            if (threadIdx.x == 0) v[k] = s;
+        }
+    }
     return true;
 }
 
@@ -3123,7 +3149,7 @@ void launch_spmv_v(const DevSchedule &d, const double *Ap, size_t a_stride, Kryl
 static SpmvSums fused_sums(const DevSchedule &d, bool fused, int spmv_variant) {
     if (!fused) return SpmvSums{0, 0};
     const int g = fuse_blocks(d.fuse_n0, variant_waves(spmv_variant));
-    return SpmvSums{2 * g, (g + 31) / 32};
+    return SpmvSums{2 * g, sum_groups(g, variant_waves(spmv_variant))};
 }
 
 int wells_fix_at(const DevSchedule &d, int spmv_variant) {

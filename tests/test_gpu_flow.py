@@ -307,3 +307,22 @@ def test_patterns_without_the_transposed_blocks(n, ordering):
             assert st == rs.OK
             got.append((x, info[0]["half_steps"]))
     assert np.array_equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
+
+
+@pytest.mark.parametrize("grid", [(5, 4, 3), (21, 16, 8), (23, 17, 11)])
+def test_one_and_four_wave_products_give_the_same_sums(grid):
+    """The partials of a product's dot products are those of four waves in
+    workgroups of one (kept apart, 128 a group) as in workgroups of four."""
+    s = make_grid_system(*grid, active_frac=0.9, nnc_frac=0.03, seed=grid[0])
+    for ordering in (rs.ORDER_GRAPH_COLOUR, rs.ORDER_LEVEL_SET):
+        with rs.Solver(s.rowptr, s.colidx, s.vals, ordering=ordering) as sol:
+            sol.factor()
+            got = []
+            for graph in (0, 1):
+                rs.ilu0_set_option(sol.M, rs.OPT_USE_GRAPH, graph)
+                for variant in (0, 2, 6, 8):
+                    rs.ilu0_set_option(sol.M, rs.OPT_SPMV_VARIANT, variant)
+                    x, st, info = sol.solve(s.b[:, 0], reduction=1e-8)
+                    got.append((x, st, info[0]["half_steps"], info[0]["final_norm"], info[0]["true_rel_residual"]))
+        for g in got[1:]:
+            assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:]
