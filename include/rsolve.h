@@ -369,11 +369,11 @@ int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t 
  * forbid hipMalloc): the same kernels and the same results bit for bit,
  * with v and z device pointers (caller order, n_sys * n_brows * 3 doubles,
  * caller-owned) and every intermediate (the new-order input and output, the
- * lower sweep's y, the single-launch sweeps' tile flags and counters) in a
+ * lower sweep's y, the single-launch sweeps' counters) in a
  * fixed workspace of RS_NOALLOC_SCRATCH_BYTES that the library holds on
  * each GPU it runs on until the process ends.  Calls no hipMalloc, hipFree
  * or allocating library routine.  n_sys systems of n_brows block rows need
- * about 72 * n_brows * n_sys bytes (3 vectors) plus 8 bytes per sweep tile:
+ * about 72 * n_brows * n_sys bytes (3 vectors):
  * up to about 1.1M block rows for one system; larger calls return
  * RS_OUT_OF_MEMORY with the sizes in rsolve_last_error().  Every call on a
  * GPU shares that GPU's workspace, whatever the handle: calls that overlap
