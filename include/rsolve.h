@@ -31,6 +31,8 @@
  *     caller memory.
  *   - `stream` is a hipStream_t (NULL = the default stream).  Calls that
  *     return a status read from the device (factor, solve) synchronise it.
+ *     ilu0_apply and the solves return RS_HIP_ERROR for a stream that is
+ *     being captured, and queue nothing.
  *   - Handles own every device buffer they allocate.  A handle must not be
  *     used from two host threads at once.
  *   - Block size is 3; indices are int32; values FP64, block-row-major.

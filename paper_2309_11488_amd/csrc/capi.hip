@@ -831,6 +831,19 @@ static int after_apply(ilu0_t M, hipStream_t s) {
     return RS_OK;
 }
 
+// The calls that wait for their stream end with an error in a capture; they
+// end before any work, so that nothing the handle notes as done (y marked) is
+// only recorded.
+static int refuse_capture(hipStream_t s, const char *call) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return RS_OK;
+    }
+    if (cap == hipStreamCaptureStatusNone) return RS_OK;
+    return fail(RS_HIP_ERROR, std::string(call) + ": the stream is being captured");
+}
+
 static int check_pair(ilu0_t M, bcsr_t A) {
     if (!M || !A) return fail(RS_INVALID_ARG, "NULL handle");
     if (M->hash != A->hash || M->n != A->n || M->nnzb != A->nnzb)
@@ -1598,8 +1611,9 @@ int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t 
     if (!M->factored) return fail(RS_NOT_FACTORED, "ilu0_apply: not factored");
     if (n_sys == 0 || M->n == 0) return RS_OK;
     hipStream_t s = (hipStream_t)stream;
-    int st = after_apply(M, s);
+    int st = refuse_capture(s, "ilu0_apply");
     if (st != RS_OK) return st;
+    if ((st = after_apply(M, s)) != RS_OK) return st;
     if ((st = ensure_workspace(M, s)) != RS_OK) return st;
     if (reads_u(M, false) && (st = ensure_u(M, s)) != RS_OK) return st;
     const size_t m = 3 * (size_t)M->n * n_sys;
@@ -1630,11 +1644,8 @@ int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t 
     // Only single-launch sweeps leave a word to read, and host vectors need
     // the copy's end; a device caller's stream goes on without the host
     // (200 000 cells, an application and a product: 95 -> 70 us).  An event
-    // keeps the handle's next call behind this one.  A capture is refused
-    // here as it always was: the wait below is not allowed in one.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
-    const bool capturing = hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
-    if (M->tile_sweeps || mem != RS_MEM_DEVICE || capturing) return sweep_error(M, s);
+    // keeps the handle's next call behind this one.
+    if (M->tile_sweeps || mem != RS_MEM_DEVICE) return sweep_error(M, s);
     if (!M->ev_apply) HIP_TRY(hipEventCreateWithFlags(&M->ev_apply, hipEventDisableTiming));
     HIP_TRY(hipEventRecord(M->ev_apply, s));
     return RS_OK;
@@ -1771,6 +1782,7 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
         return RS_OK;
     }
     hipStream_t s = (hipStream_t)stream;
+    if ((st = refuse_capture(s, "bicgstab_solve")) != RS_OK) return st;
     if ((st = after_apply(M, s)) != RS_OK) return st;
     st = ensure_workspace(M, s);
     if (st != RS_OK) return st;
@@ -2028,6 +2040,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         return RS_OK;
     }
     hipStream_t s = (hipStream_t)stream;
+    if ((st = refuse_capture(s, "gmres_solve")) != RS_OK) return st;
     if ((st = after_apply(M, s)) != RS_OK) return st;
     st = ensure_workspace(M, s);
     if (st != RS_OK) return st;
