@@ -163,7 +163,9 @@ enum rs_option {
                                 RS_ZERO_PIVOT in the statuses of the next solve, and
                                 ilu0_factor_status waits for it and gives what the waiting call
                                 would have returned.  A solve or application on another stream
-                                must wait for the factorisation's stream first. */
+                                must wait for the factorisation's stream first (a graph that
+                                captured it is launched behind applications queued on the
+                                captured stream). */
     RS_OPT_LOWER_PARTS = 14  /* 1 (default): with FP64 factors, in BiCGStab's fused iteration on a
                                 pattern of RS_OPT_Y_INPUT_PATTERN, the SpMV v = A phat also forms,
                                 from the same FP64 blocks, the sums sum_k A'_ik inv(U_kk) r_k and

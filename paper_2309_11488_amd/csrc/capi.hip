@@ -240,6 +240,7 @@ struct rs_ilu0 {
     // the last application queued without a host wait: the next call may use
     // another stream, and works in the same buffers
     hipEvent_t ev_apply = nullptr;
+    bool apply_queued = false;
     // solve workspace
     DevBuf work, ywork, ywork2, ftickets, vpart, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
     bool y_marked = false;     // ywork holds the mark everywhere (single-launch sweeps)
@@ -825,9 +826,24 @@ static double factor_time(ilu0_t M) {
 }
 
 // Order `s` after the handle's last queued application (ilu0_apply), whatever
-// stream that was on.
+// stream that was on.  A stream being captured may not depend on work outside
+// its capture: there the host waits for the application (in the relaxed mode,
+// since the wait is none of the capture's business).  The runtime refuses that
+// for an application queued on the captured stream itself; what the capture
+// records then comes after it by the order of the caller's launch.
 static int after_apply(ilu0_t M, hipStream_t s) {
-    if (M->ev_apply) HIP_TRY(hipStreamWaitEvent(s, M->ev_apply, 0));
+    if (!M->apply_queued) return RS_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap == hipStreamCaptureStatusNone) {
+        HIP_TRY(hipStreamWaitEvent(s, M->ev_apply, 0));
+        return RS_OK;
+    }
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
+    if (hipEventSynchronize(M->ev_apply) == hipSuccess) M->apply_queued = false;
+    else (void)hipGetLastError();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
     return RS_OK;
 }
 
@@ -1615,7 +1631,8 @@ int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t 
     if (st != RS_OK) return st;
     if ((st = after_apply(M, s)) != RS_OK) return st;
     if ((st = ensure_workspace(M, s)) != RS_OK) return st;
-    if (reads_u(M, false) && (st = ensure_u(M, s)) != RS_OK) return st;
+    const bool fills_u = reads_u(M, false) && M->u_missing;
+    if (fills_u && (st = ensure_u(M, s)) != RS_OK) return st;
     const size_t m = 3 * (size_t)M->n * n_sys;
     const double *vd = nullptr;
     st = stage_in(v, mem, M->bstage, m, s, &vd);
@@ -1644,10 +1661,14 @@ int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t 
     // Only single-launch sweeps leave a word to read, and host vectors need
     // the copy's end; a device caller's stream goes on without the host
     // (200 000 cells, an application and a product: 95 -> 70 us).  An event
-    // keeps the handle's next call behind this one.
+    // keeps the handle's next call behind this one.  The one application of a
+    // factorisation that fills in U waits for it, so that other streams (and
+    // captures, which cannot wait for the event) find it in place.
     if (M->tile_sweeps || mem != RS_MEM_DEVICE) return sweep_error(M, s);
+    if (fills_u) HIP_TRY(hipStreamSynchronize(s));
     if (!M->ev_apply) HIP_TRY(hipEventCreateWithFlags(&M->ev_apply, hipEventDisableTiming));
     HIP_TRY(hipEventRecord(M->ev_apply, s));
+    M->apply_queued = true;
     return RS_OK;
 }
 
@@ -1723,7 +1744,8 @@ int ilu0_apply_noalloc(ilu0_t M, const double *v, double *z, int32_t first_sys, 
     int st = noalloc_scratch(&base);
     if (st != RS_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    if ((st = after_apply(M, s)) != RS_OK) return st;
+    // shares with the handle's queued applications only the factors, which
+    // those leave whole (see ilu0_apply)
     if (reads_u(M, false) && (st = ensure_u(M, s)) != RS_OK) return st;
     Krylov k{};
     k.vstride = rs::vec_stride(M->n);
