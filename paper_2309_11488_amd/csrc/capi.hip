@@ -240,6 +240,7 @@ struct rs_ilu0 {
     // the last application queued without a host wait: the next call may use
     // another stream, and works in the same buffers
     hipEvent_t ev_apply = nullptr;
+    hipStream_t apply_stream = nullptr;   // its stream, only asked whether it is being captured
     bool apply_queued = false;
     // solve workspace
     DevBuf work, ywork, ywork2, ftickets, vpart, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
@@ -825,25 +826,31 @@ static double factor_time(ilu0_t M) {
     return hipEventElapsedTime(&ms, M->ev_f0, M->ev_f1) == hipSuccess ? ms : 0.0;
 }
 
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    return cap != hipStreamCaptureStatusNone;
+}
+
 // Order `s` after the handle's last queued application (ilu0_apply), whatever
 // stream that was on.  A stream being captured may not depend on work outside
 // its capture: there the host waits for the application (in the relaxed mode,
-// since the wait is none of the capture's business).  The runtime refuses that
-// for an application queued on the captured stream itself; what the capture
-// records then comes after it by the order of the caller's launch.
+// since the wait is none of the capture's business).  That wait would
+// invalidate a capture of the application's own stream; what such a capture
+// records comes after the application by the order of the caller's launch.
 static int after_apply(ilu0_t M, hipStream_t s) {
     if (!M->apply_queued) return RS_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-    if (cap == hipStreamCaptureStatusNone) {
+    if (!capturing(s)) {
         HIP_TRY(hipStreamWaitEvent(s, M->ev_apply, 0));
         return RS_OK;
     }
+    if (capturing(M->apply_stream)) return RS_OK;
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
-    if (hipEventSynchronize(M->ev_apply) == hipSuccess) M->apply_queued = false;
-    else (void)hipGetLastError();
+    const hipError_t e = hipEventSynchronize(M->ev_apply);
     (void)hipThreadExchangeStreamCaptureMode(&mode);
+    HIP_TRY(e);
+    M->apply_queued = false;
     return RS_OK;
 }
 
@@ -851,12 +858,7 @@ static int after_apply(ilu0_t M, hipStream_t s) {
 // end before any work, so that nothing the handle notes as done (y marked) is
 // only recorded.
 static int refuse_capture(hipStream_t s, const char *call) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return RS_OK;
-    }
-    if (cap == hipStreamCaptureStatusNone) return RS_OK;
+    if (!capturing(s)) return RS_OK;
     return fail(RS_HIP_ERROR, std::string(call) + ": the stream is being captured");
 }
 
@@ -1668,6 +1670,7 @@ int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t 
     if (fills_u) HIP_TRY(hipStreamSynchronize(s));
     if (!M->ev_apply) HIP_TRY(hipEventCreateWithFlags(&M->ev_apply, hipEventDisableTiming));
     HIP_TRY(hipEventRecord(M->ev_apply, s));
+    M->apply_stream = s;
     M->apply_queued = true;
     return RS_OK;
 }
