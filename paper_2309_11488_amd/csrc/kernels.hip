@@ -1238,8 +1238,10 @@ __global__ void __launch_bounds__(kRowThreads) k_factor_flow(DevSchedule d, cons
             double lv[FM][3], uv[FM][3], up0[FM][3];
             uint64_t dv[FM][3];
             int dq[FM], code0[FM], src0[FM], un[FM], u0[FM];
-            // simple: every lower block updates the row's diagonal only, from
-            // a block of A' (a grid's rows)
+            // simple: every lower block updates the row's diagonal, and that
+            // only, from a block of A' (a grid's rows; a block without an
+            // update is not one: an infinite L times the zero that stands for
+            // an absent update would reach the pivot)
             bool simple = true;
 #pragma unroll
             for (int t = 0; t < FM; ++t) {
@@ -1254,6 +1256,7 @@ __global__ void __launch_bounds__(kRowThreads) k_factor_flow(DevSchedule d, cons
                     dq[t] = d.ldq[e0 + t];
                     u0[t] = d.upd_ptr[e0 + t];
                     un[t] = d.upd_ptr[e0 + t + 1];
+                    simple = simple && un[t] - u0[t] == 1;
                 }
             }
 #pragma unroll
@@ -1267,7 +1270,7 @@ __global__ void __launch_bounds__(kRowThreads) k_factor_flow(DevSchedule d, cons
                     code0[t] = d.upd[2 * u0[t]];
                     src0[t] = d.upd[2 * u0[t] + 1];
                     if (src0[t] < 0) row3_load(Aps + (size_t)~src0[t] * 9 + 3 * r, up0[t]);
-                    simple = simple && un[t] - u0[t] == 1 && (code0[t] & 3) == 1 && src0[t] < 0;
+                    simple = simple && (code0[t] & 3) == 1 && src0[t] < 0;
                 }
             for (;;) {
                 bool miss = false;

@@ -326,3 +326,28 @@ def test_one_and_four_wave_products_give_the_same_sums(grid):
                     got.append((x, st, info[0]["half_steps"], info[0]["final_norm"], info[0]["true_rel_residual"]))
         for g in got[1:]:
             assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:]
+
+
+def test_lower_blocks_without_updates_leave_the_pivot_alone():
+    """A lower block whose transposed block is not stored updates nothing, so
+    an infinite one (1e250 times an inverse of 1e100) stays out of its row's
+    pivot in the single-launch factorisation too."""
+    n = 6
+    pairs = sorted({(i, i) for i in range(n)} | {(i, j) for i in range(1, n) for j in (i - 1, i + 1) if 1 <= j < n} | {(5, 0)})
+    rowptr = np.searchsorted([i for i, _ in pairs], np.arange(n + 1)).astype(np.int32)
+    colidx = np.array([j for _, j in pairs], np.int32)
+    rng = np.random.default_rng(3)
+    vals = rng.uniform(-1, 1, (1, len(pairs), 3, 3)) / 9.0
+    for p, (i, j) in enumerate(pairs):
+        if i == j:
+            vals[0, p] += 2.0 * np.eye(3)
+    vals[0, pairs.index((0, 0))] = np.eye(3) * 1e-100
+    vals[0, pairs.index((5, 0))] = 1e250
+    want = oracle.ilu0(rowptr, colidx, vals[0])
+    assert want[0] == oracle.OK and np.isinf(want[2][pairs.index((5, 0))]).all() and np.isfinite(want[3]).all()
+    with rs.Solver(rowptr, colidx, vals, ordering=rs.ORDER_NATURAL) as s:
+        st, bad = s.factor()
+        assert st == rs.OK and bad[0] == -1
+        lu, dinv = rs.ilu0_get_factors(s.M, 0, n, len(pairs))
+    assert np.isinf(lu[pairs.index((5, 0))]).all()
+    assert rel_block_err(dinv[1:], want[3][1:]) <= 1e-12
