@@ -121,12 +121,13 @@ enum rs_option {
                                 its partial and a one-workgroup kernel adds them; 2 = each wave
                                 stores its partial and every workgroup of the next vector kernel
                                 adds them (few partials: small systems) */
-    RS_OPT_SPIN_LIMIT = 8,   /* polls before a single-launch sweep's dependency wait gives up
-                                (default 4194304, >= 0).  A wait that gives up lets its tile go
-                                on, so the launch still ends; the solve then returns RS_HIP_ERROR
-                                and the handle's sweep counters and marks are reset, so the
-                                next call starts clean.  A small value forces that error path
-                                (for tests of the recovery) */
+    RS_OPT_SPIN_LIMIT = 8,   /* polls before a dependency wait of a single-launch sweep, application
+                                or factorisation gives up (default 4194304, >= 0).  A wait that
+                                gives up lets its tile go on, so the launch still ends; the call
+                                then returns RS_HIP_ERROR (a queued factorisation's next solve and
+                                ilu0_factor_status do) and the handle's counters and marks are
+                                reset, so the next call starts clean.  A small value forces that
+                                error path (for tests of the recovery) */
     RS_OPT_FUSE_SPMV = 9,    /* 1 (default): where the rows without lower blocks are the first rows
                                 of the analysed order (at least a quarter of them) and share one
                                 upper level (graph colouring of a grid: the first colour),
@@ -160,7 +161,8 @@ enum rs_option {
     RS_OPT_FACTOR_ASYNC = 13, /* 0 (default): ilu0_factor waits for the factorisation and returns its
                                 status.  1: ilu0_factor only queues it on its stream and returns
                                 RS_OK (bad_row untouched); a singular pivot then shows as
-                                RS_ZERO_PIVOT in the statuses of the next solve, and
+                                RS_ZERO_PIVOT in the statuses of the next solve (RS_HIP_ERROR
+                                when a dependency wait gave up), and
                                 ilu0_factor_status waits for it and gives what the waiting call
                                 would have returned.  A solve or application on another stream
                                 must wait for the factorisation's stream first (a graph that

@@ -927,7 +927,7 @@ int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *ba
                                    f32 ? M->Uf.as<float>() : nullptr, f32 ? M->Dinvf.as<float>() : nullptr,
                                    M->bad.as<int32_t>(), skip_u0,
                                    std::find(S.lnarrow.begin(), S.lnarrow.end(), 0) == S.lnarrow.end(), S.nl_levels,
-                                   M->fctr.as<rs::SweepCtr>(), M->batch, s);
+                                   M->spin_limit, M->fctr.as<rs::SweepCtr>(), M->batch, s);
         else
             rs::launch_gather_pairs(A->vals.as<double>(), per, M->pvals.as<double>(), per, d.rest_dst, d.rest_src,
                                     d.nrest, M->batch, s);
@@ -1787,6 +1787,7 @@ int ilu0_apply_noalloc(ilu0_t M, const double *v, double *z, int32_t first_sys, 
 }
 
 static int status_rank(int s) {
+    if (s == RS_HIP_ERROR) return 5;   // a queued factorisation's wait gave up
     if (s < 0) return 4;
     if (s == RS_BREAKDOWN) return 3;
     if (s == RS_NOT_CONVERGED) return 2;
@@ -1896,6 +1897,7 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
     }
     // the prediction learns from converged solves only, and stays small
     if (worst == RS_OK) M->last_iters = std::min(needed, kPredictMax);
+    if (worst == RS_HIP_ERROR) factor_message(worst);
     return worst;
 }
 
@@ -2206,6 +2208,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         needed = std::max(needed, S.half_steps);
     }
     if (worst == RS_OK) M->last_gm_steps = std::min(needed, kPredictMax);
+    if (worst == RS_HIP_ERROR) factor_message(worst);
     return worst;
 }
 

@@ -220,11 +220,11 @@ void launch_factor_first(const DevSchedule &d, const double *A, size_t a_stride,
 constexpr int32_t kNoBadRow = 0x7f7f7f7f, kBadWait = -2;
 // The whole factorisation as two launches: A' and the marks, then every row
 // in dependency order (levels: of the lower schedule; narrow: no row holds
-// more than 6 lower or 6 upper blocks).  Sets bad itself.  Arguments
-// otherwise as launch_factor_level.
+// more than 6 lower or 6 upper blocks; spin: polls before a wait gives up).
+// Sets bad itself.  Arguments otherwise as launch_factor_level.
 void launch_factor_flow(const DevSchedule &d, const double *A, size_t a_stride, double *Ap, double *L, double *U,
                         double *Dinv, float *Lf, float *Uf, float *Df, int32_t *bad, bool skip_u0, bool narrow,
-                        int levels, SweepCtr *ctr, int nsys, hipStream_t s);
+                        int levels, int spin, SweepCtr *ctr, int nsys, hipStream_t s);
 // U[f] = A'[usrc[f]], rounded to T, for U positions [f0, f1) of every
 // system (per-system strides a_stride and u_stride, in elements).
 template <typename T>

@@ -2371,7 +2371,7 @@ __global__ void __launch_bounds__(kVecThreads) k_setup(int n, const int32_t *__r
         S.rho = v[0]; S.rho_old = 1.0; S.alpha = 1.0; S.omega = 1.0;
         S.beta = (S.rho / S.rho_old) * (S.alpha / S.omega);
         S.half_steps = 0; S.iter = 1; S.max_iter = max_iter; S.true_res = 0.0;
-        if (bad && bad[sys] < n) { S.status = RS_ZERO_PIVOT; S.phase = PH_DONE; }
+        if (bad && bad[sys] < n) { S.status = bad[sys] == kBadWait ? RS_HIP_ERROR : RS_ZERO_PIVOT; S.phase = PH_DONE; }
         else if (!finite(r0)) { S.status = RS_NON_FINITE; S.phase = PH_DONE; }
         else if (r0 == 0.0) { S.status = RS_OK; S.phase = PH_DONE; }
         else if (max_iter <= 0) { S.status = RS_NOT_CONVERGED; S.phase = PH_DONE; }
@@ -3063,7 +3063,7 @@ template void launch_usweep_flow<float>(const DevSchedule &, const float *, size
                                         hipStream_t, hipEvent_t, hipEvent_t);
 void launch_factor_flow(const DevSchedule &d, const double *A, size_t a_stride, double *Ap, double *L, double *U,
                         double *Dinv, float *Lf, float *Uf, float *Df, int32_t *bad, bool skip_u0, bool narrow,
-                        int levels, SweepCtr *ctr, int nsys, hipStream_t s) {
+                        int levels, int spin, SweepCtr *ctr, int nsys, hipStream_t s) {
     if (d.nlt <= 0 || nsys <= 0) return;
     k_factor_flow_prep<<<dim3(copy_blocks((size_t)d.nnzb * 9), nsys), kRowThreads, 0, s>>>(d, A, a_stride, Ap, Dinv,
                                                                                           bad, ctr);
@@ -3071,7 +3071,7 @@ void launch_factor_flow(const DevSchedule &d, const double *A, size_t a_stride, 
     const dim3 g(flow_grid(one, kFlowGrid, d.nlt * nsys));
     auto go = [&](auto F32, auto FM, auto ONE) {
         k_factor_flow<decltype(F32)::value, decltype(FM)::value, decltype(ONE)::value><<<g, kRowThreads, 0, s>>>(
-            d, Ap, L, U, Dinv, Lf, Uf, Df, bad, skip_u0 ? 1 : 0, ctr, nsys, kSpinLimitDefault);
+            d, Ap, L, U, Dinv, Lf, Uf, Df, bad, skip_u0 ? 1 : 0, ctr, nsys, spin);
     };
     auto scope = [&](auto F32, auto FM) {
         if (one) go(F32, FM, std::true_type{}); else go(F32, FM, std::false_type{});

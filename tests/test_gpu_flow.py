@@ -351,3 +351,41 @@ def test_lower_blocks_without_updates_leave_the_pivot_alone():
         lu, dinv = rs.ilu0_get_factors(s.M, 0, n, len(pairs))
     assert np.isinf(lu[pairs.index((5, 0))]).all()
     assert rel_block_err(dinv[1:], want[3][1:]) <= 1e-12
+
+
+def test_single_launch_factorisation_recovers_from_a_wait_that_gives_up():
+    """RS_OPT_SPIN_LIMIT bounds the factorisation's waits too: one that gives
+    up is RS_HIP_ERROR from the factorisation, or when it was only queued from
+    the next solve and ilu0_factor_status, and the next factorisation is sound."""
+    s = make_grid_system(17, 13, 9, active_frac=0.85, nnc_frac=0.03, seed=4)
+    nnzb = len(s.colidx)
+    with rs.Solver(s.rowptr, s.colidx, s.vals, ordering=rs.ORDER_LEVEL_SET) as sol:
+        sol.factor()
+        want, x0 = rs.ilu0_get_factors(sol.M, 0, s.n, nnzb), sol.solve(s.b[:, 0])[0]
+        default = rs.ilu0_get_option(sol.M, rs.OPT_SPIN_LIMIT)
+        rs.ilu0_set_option(sol.M, rs.OPT_SPIN_LIMIT, 0)
+        with pytest.raises(rs.RsolveError) as e:
+            for _ in range(5):
+                sol.factor()
+        assert e.value.status == rs.HIP_ERROR
+        rs.ilu0_set_option(sol.M, rs.OPT_FACTOR_ASYNC, 1)
+        gave_up = False
+        for _ in range(5):
+            rs.ilu0_set_option(sol.M, rs.OPT_SPIN_LIMIT, 0)
+            assert sol.factor()[0] == rs.OK
+            rs.ilu0_set_option(sol.M, rs.OPT_SPIN_LIMIT, default)
+            try:
+                sol.solve(s.b[:, 0])
+            except rs.RsolveError as err:
+                assert err.status == rs.HIP_ERROR
+                with pytest.raises(rs.RsolveError) as e:
+                    rs.ilu0_factor_status(sol.M, 1)
+                assert e.value.status == rs.HIP_ERROR
+                gave_up = True
+                break
+        assert gave_up
+        sol.factor()
+        got = rs.ilu0_get_factors(sol.M, 0, s.n, nnzb)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+        x, st, _ = sol.solve(s.b[:, 0])
+        assert st == rs.OK and np.array_equal(x, x0) and rs.ilu0_factor_status(sol.M, 1)[0] == rs.OK
