@@ -122,8 +122,9 @@ enum rs_option {
                                 stores its partial and every workgroup of the next vector kernel
                                 adds them (few partials: small systems) */
     RS_OPT_SPIN_LIMIT = 8,   /* polls before a dependency wait of a single-launch sweep, application
-                                or factorisation gives up (default 4194304, >= 0).  A wait that
-                                gives up lets its tile go on, so the launch still ends; the call
+                                or factorisation, or a reduction's wait for its partials, gives
+                                up (default 4194304, >= 0).  A wait that gives up lets its
+                                workgroup go on, so the launch still ends; the call
                                 then returns RS_HIP_ERROR (a queued factorisation's next solve and
                                 ilu0_factor_status do) and the handle's counters and marks are
                                 reset, so the next call starts clean.  A small value forces that

@@ -286,6 +286,10 @@ struct rs_ilu0 {
     std::vector<int32_t> h_wfix;   // rows below fuse_n0 that a perforation couples
     rs::WellsDev wdev{};
     int split() const { return reduce_split; }
+    // polled partials of the vector and of the GMRES kernels
+    size_t vpart_stride() const { return 2 * (size_t)rs::vec_blocks(n); }
+    size_t vpart_bytes() const { return (size_t)batch * vpart_stride() * sizeof(double); }
+    size_t gm_vpart_bytes() const { return (size_t)batch * rs::gm_poll_stride() * sizeof(double); }
     // a BiCGStab iteration captured as HIP graphs, replayed on the caller's
     // stream: one segment per set of consecutive parts of the iteration (the
     // whole iteration, or the runs between the parts of a kernel class that
@@ -1067,16 +1071,15 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
         HIP_TRY(M->ctrs.alloc(2 * sizeof(rs::SweepCtr)));
         HIP_TRY(hipMemsetAsync(M->ctrs.p, 0, 2 * sizeof(rs::SweepCtr), s));
     }
-    const size_t vps = 2 * (size_t)rs::vec_blocks(M->n);
     if (!M->vpart.p) {
-        HIP_TRY(M->vpart.alloc(B * vps * sizeof(double)));
-        rs::launch_flow_mark(M->vpart.p, B * vps * sizeof(double), s);
+        HIP_TRY(M->vpart.alloc(M->vpart_bytes()));
+        rs::launch_flow_mark(M->vpart.p, M->vpart_bytes(), s);
         HIP_TRY(hipGetLastError());
     }
     double *w = M->work.as<double>();
     Krylov &k = M->k;
     k.vpart = M->vpart.as<double>();
-    k.vpart_stride = vps;
+    k.vpart_stride = M->vpart_stride();
     k.r = w; k.rhat = w + vec; k.p = w + 2 * vec; k.v = w + 3 * vec; k.phat = w + 4 * vec;
     k.s = w + 5 * vec; k.shat = w + 6 * vec; k.t = w + 7 * vec; k.x = w + 8 * vec;
     k.vstride = vs;
@@ -1094,6 +1097,7 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
     k.fpart_stride = fstride;
     k.lp = M->lpwork.p ? M->lpwork.as<double>() : nullptr;
     k.st = M->state.as<SysState>();
+    k.spin = M->spin_limit;
     k.lctr = M->ctrs.as<rs::SweepCtr>();
     k.uctr = k.lctr + 1;
     // single-launch sweeps find y marked and leave it so; per-level sweeps
@@ -1107,13 +1111,30 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
     return RS_OK;
 }
 
-// After a single-launch sweep gave up a dependency wait: clear the sweep
-// counters and have y marked again, once the stream has drained.
+// After a wait gave up: clear the sweep counters and have y marked again, once
+// the stream has drained.
 static int sweep_reset(ilu0_t M, hipStream_t s) {
     HIP_TRY(hipMemsetAsync(M->ctrs.p, 0, 2 * sizeof(rs::SweepCtr), s));
     M->y_marked = false;
     HIP_TRY(hipStreamSynchronize(s));
     return fail(RS_HIP_ERROR, "sweep dependency wait exceeded its limit");
+}
+
+// After a solve (its states and, with `ctrs`, the sweep counters are on the
+// host): RS_HIP_ERROR when one of its waits gave up, with everything a late
+// store of that launch may have touched set anew.
+static int solve_waits(ilu0_t M, bool ctrs, hipStream_t s) {
+    int st = RS_OK;
+    if (ctrs && (M->h_ctr[0].error || M->h_ctr[1].error)) st = sweep_reset(M, s);
+    bool gave_up = false;
+    for (int i = 0; i < M->batch; ++i) gave_up = gave_up || M->h_state[i].gave_up;
+    if (!gave_up) return st;
+    HIP_TRY(hipMemsetAsync(M->state.p, 0, (size_t)M->batch * sizeof(SysState), s));
+    rs::launch_flow_mark(M->vpart.p, M->vpart_bytes(), s);
+    if (M->gm_vpart.p) rs::launch_flow_mark(M->gm_vpart.p, M->gm_vpart_bytes(), s);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(s));
+    return st != RS_OK ? st : fail(RS_HIP_ERROR, "reduction wait exceeded its limit");
 }
 
 // Events bracketing a solve call on its stream (created on first use); the
@@ -1886,7 +1907,7 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
         st = finish();
         if (st != RS_OK) return st;
     }
-    if ((M->tile_sweeps || flow) && (M->h_ctr[0].error || M->h_ctr[1].error)) return sweep_reset(M, s);
+    if ((st = solve_waits(M, M->tile_sweeps || flow, s)) != RS_OK) return st;
     const double solve_ms = elapsed_ms(M->ev_s0, M->ev_s1);
     int worst = RS_OK, needed = 1;
     for (int i = 0; i < B; ++i) {
@@ -2092,13 +2113,13 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
     HIP_TRY(M->gm_state.alloc((size_t)B * sizeof(rs::GmState)));
     HIP_TRY(M->gm_part.alloc((size_t)B * rs::gm_part_stride() * sizeof(double)));
     if (!M->gm_vpart.p) {
-        const size_t bytes = (size_t)B * rs::gm_poll_stride() * sizeof(double);
-        HIP_TRY(M->gm_vpart.alloc(bytes));
-        rs::launch_flow_mark(M->gm_vpart.p, bytes, s);
+        HIP_TRY(M->gm_vpart.alloc(M->gm_vpart_bytes()));
+        rs::launch_flow_mark(M->gm_vpart.p, M->gm_vpart_bytes(), s);
         HIP_TRY(hipGetLastError());
     }
     rs::GmWork g{M->gm_basis.as<double>(), colstride, k.vstride, M->gm_part.as<double>(), rs::gm_part_stride(),
-                 k.tickets, k.ticket_stride, M->gm_vpart.as<double>(), M->gm_state.as<rs::GmState>(), k.st};
+                 k.tickets, k.ticket_stride, M->gm_vpart.as<double>(), M->gm_state.as<rs::GmState>(), k.st,
+                 M->spin_limit};
     const size_t m = 3 * (size_t)M->n * B;
     const double *bd = nullptr;
     st = stage_in(b, mem, M->bstage, m, s, &bd);
@@ -2198,7 +2219,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         st = finish();
         if (st != RS_OK) return st;
     }
-    if ((M->tile_sweeps || flow.on) && (M->h_ctr[0].error || M->h_ctr[1].error)) return sweep_reset(M, s);
+    if ((st = solve_waits(M, M->tile_sweeps || flow.on, s)) != RS_OK) return st;
     const double solve_ms = elapsed_ms(M->ev_s0, M->ev_s1);
     int worst = RS_OK, needed = 1;
     for (int i = 0; i < B; ++i) {

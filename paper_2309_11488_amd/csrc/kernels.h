@@ -19,7 +19,8 @@ struct SysState {
     double r0norm, tol, last_norm;
     double true_res;
     int32_t phase, status, half_steps, iter;
-    int32_t max_iter, pad0;
+    int32_t max_iter;
+    int32_t gave_up;   // a polled reduction gave up waiting; set on the device, cleared by the host
 };
 
 // Device copies of the schedule (see analysis.h for the meaning).
@@ -107,6 +108,7 @@ struct Krylov {
     size_t fpart_stride;
     double *lp;         // lower parts of the second application (k_spmv_lp): 6 values per row, 2 vstride per system, or NULL
     SysState *st;       // nsys states
+    int spin;           // polls before a reduction of the vector kernels gives up
     SweepCtr *lctr, *uctr;
 };
 
@@ -404,6 +406,7 @@ struct GmWork {
     double *vpart;       // partials that a workgroup polls (marked between launches), gm_poll_stride per system
     GmState *gm;
     SysState *st;
+    int spin;            // polls before such a reduction gives up
 };
 constexpr int kGmPollBlocks = 512;
 constexpr size_t gm_poll_stride() { return (size_t)(kGmMax + 1) * kGmPollBlocks; }

@@ -2244,12 +2244,17 @@ __device__ inline void sum_products(const double *__restrict__ p, int np, const 
 // again.  A store and a load, where the ticket tree takes a store, its
 // acknowledgement and an atomic on each of two levels.  No other
 // workgroup waits, so the polls end whatever the number of resident
-// workgroups; they are bounded all the same (a partial left marked is a
-// NaN, and the solve reports it).  A half- or full-step update of 4 000 cells
+// workgroups; they are bounded all the same (`spin` polls, RS_OPT_SPIN_LIMIT).
+// A poll that gives up sets the system's gave_up, which the host answers by
+// marking every partial anew once the stream has drained (a partial that
+// comes late must not pass for a later reduction's), and gives NaN, which
+// ends the system's solve.  A half- or full-step update of 4 000 cells
 // takes 8.3 instead of 9.8 us, of 96k cells 9.1 instead of 10.7.
 template <int NV>
-__device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx) {
+__device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx, int spin, SysState &S) {
     __shared__ double lds[16 * NV];
+    __shared__ int gave_up;
+    if (threadIdx.x == 0) gave_up = 0;
     block_sum<NV>(v, lds);
     if (threadIdx.x == 0)
         for (int k = 0; k < NV; ++k) flow_store<false>(part + (size_t)bx * NV + k, v[k]);
@@ -2258,7 +2263,7 @@ __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx) {
     constexpr int U = NV <= 4 ? 4 : 1;
     for (int b0 = 0; b0 < nblk; b0 += U * (int)blockDim.x) {
         uint64_t t[U][NV];
-        for (int spins = 0; spins < kSpinLimitDefault; ++spins) {
+        for (int spins = 0;; ++spins) {
             bool miss = false;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -2269,6 +2274,10 @@ __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx) {
             for (int u = 0; u < U; ++u)
                 for (int k = 0; k < NV; ++k) miss |= t[u][k] == FlowBits<double>::mark;
             if (!__any(miss)) break;
+            if (spins >= spin) {
+                gave_up = 1;
+                break;
+            }
             asm volatile("" ::: "memory");
         }
         // kGroup = 32 consecutive partials sit in one half of a wave
@@ -2284,6 +2293,13 @@ __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx) {
         }
     }
     __syncthreads();   // every thread has read its partials
+    if (gave_up) {
+        if (threadIdx.x == 0) {
+            S.gave_up = 1;
+            for (int k = 0; k < NV; ++k) v[k] = __builtin_nan("");
+        }
+        return true;
+    }
     for (int e = threadIdx.x; e < nblk * NV; e += blockDim.x) flow_mark(part + e);
     if (threadIdx.x < 64) {
         const int ng = (nblk + kGroup - 1) / kGroup;
@@ -2364,7 +2380,7 @@ __global__ void __launch_bounds__(kVecThreads) k_setup(int n, const int32_t *__r
             v[0] += val[u] * val[u];
         }
     }
-    if (poll_reduce<1>(v, k.vpart + sys * k.vpart_stride, gridDim.x, bx) && threadIdx.x == 0) {
+    if (poll_reduce<1>(v, k.vpart + sys * k.vpart_stride, gridDim.x, bx, k.spin, k.st[sys]) && threadIdx.x == 0) {
         SysState &S = k.st[sys];
         const double r0 = sqrt(v[0]);
         S.r0norm = r0; S.tol = reduction * r0; S.last_norm = r0;
@@ -2455,7 +2471,7 @@ __global__ void __launch_bounds__(kVecThreads) k_s_update(Krylov k, int sums_at,
             v[0] += sv * sv;
         }
     }
-    if (poll_reduce<1>(v, k.vpart + sys * k.vpart_stride, gridDim.x, bx) && threadIdx.x == 0) {
+    if (poll_reduce<1>(v, k.vpart + sys * k.vpart_stride, gridDim.x, bx, k.spin, k.st[sys]) && threadIdx.x == 0) {
         const double sn = sqrt(v[0]);
         S.half_steps = 2 * S.iter - 1;
         S.last_norm = sn;
@@ -2550,7 +2566,7 @@ __global__ void __launch_bounds__(kVecThreads) k_xr_update(Krylov k, int sums_at
             }
         }
     }
-    if (poll_reduce<2>(v, k.vpart + sys * k.vpart_stride, gridDim.x, bx) && threadIdx.x == 0) {
+    if (poll_reduce<2>(v, k.vpart + sys * k.vpart_stride, gridDim.x, bx, k.spin, k.st[sys]) && threadIdx.x == 0) {
         // every workgroup computed the same omega: use this one's copy
         if (phase == PH_HALF) {
             if (omega_zero) S.status = RS_BREAKDOWN;
@@ -2597,7 +2613,7 @@ constexpr int kGmThreads = 256;
 // the polling workgroup).
 template <int NV>
 __device__ inline bool gm_reduce(double (&v)[NV], const GmWork &g, int sys, int nblk, int bx) {
-    if (nblk <= kGmPollBlocks) return poll_reduce<NV>(v, g.vpart + sys * gm_poll_stride(), nblk, bx);
+    if (nblk <= kGmPollBlocks) return poll_reduce<NV>(v, g.vpart + sys * gm_poll_stride(), nblk, bx, g.spin, g.st[sys]);
     return grid_reduce<NV>(v, g.part + sys * g.pstride, g.tickets + sys * g.tkstride, nblk, bx);
 }
 

@@ -389,3 +389,32 @@ def test_single_launch_factorisation_recovers_from_a_wait_that_gives_up():
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
         x, st, _ = sol.solve(s.b[:, 0])
         assert st == rs.OK and np.array_equal(x, x0) and rs.ilu0_factor_status(sol.M, 1)[0] == rs.OK
+
+
+@pytest.mark.parametrize("method", ["bicgstab", "gmres"])
+def test_polled_reduction_recovers_from_a_wait_that_gives_up(method):
+    """A reduction whose polls reach RS_OPT_SPIN_LIMIT makes the solve
+    RS_HIP_ERROR; late partials do not reach the next solve."""
+    n = 120_000
+    vals = np.tile(np.eye(3), (n, 1, 1)) * np.linspace(1.0, 2.0, n)[:, None, None]
+    b = np.random.default_rng(1).standard_normal((1, n, 3))
+    with rs.Solver(np.arange(n + 1), np.arange(n), vals, ordering=rs.ORDER_GRAPH_COLOUR) as sol:
+        rs.ilu0_set_option(sol.M, rs.OPT_FUSE_SPMV, 0)        # separate launches: only reductions wait
+        sol.factor()
+
+        def solve():
+            x, st, info = sol.solve(b, reduction=1e-6) if method == "bicgstab" else sol.solve_gmres(b, reduction=1e-6)
+            return x, st, [(i["status"], i["half_steps"], i["final_norm"], i["true_rel_residual"]) for i in info]
+
+        want = solve()
+        assert want[1] == rs.OK
+        default = rs.ilu0_get_option(sol.M, rs.OPT_SPIN_LIMIT)
+        rs.ilu0_set_option(sol.M, rs.OPT_SPIN_LIMIT, 0)
+        with pytest.raises(rs.RsolveError) as e:
+            for _ in range(10):
+                solve()
+        assert e.value.status == rs.HIP_ERROR
+        rs.ilu0_set_option(sol.M, rs.OPT_SPIN_LIMIT, default)
+        for _ in range(3):
+            got = solve()
+            assert np.array_equal(got[0], want[0]) and got[1:] == want[1:]
