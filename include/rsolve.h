@@ -328,11 +328,14 @@ typedef struct {
  * with several grid sizes, then every SpMV shape with the best sweep, then
  * the split reduction with the best of those, each
  * over `reps` (>= 1) bicgstab_solve calls on right-hand sides b (batch *
- * n_brows * 3 doubles, mem) at `reduction`.  The fastest is applied with
+ * n_brows * 3 doubles, mem) at `reduction`.  Where an iteration runs each
+ * application and its SpMV as one launch (RS_OPT_FUSE_SPMV), the sweep shapes
+ * are timed on ilu0_apply instead, and the SpMV shape is kept unless the
+ * single-launch sweep is faster.  The fastest is applied with
  * ilu0_set_option.  When the environment variable RSOLVE_TUNE_CACHE names a
  * file, results are looked up there first and appended after a search,
  * keyed by the problem shape (n, nnzb, batch, ordering, precision, sweep
- * levels) and the device.  Configurations change launch shapes only; a
+ * levels), the kind of iteration and the device.  Configurations change launch shapes only; a
  * different SpMV shape reorders the partial sums of the fused dot products
  * (results agree to rounding; each configuration is deterministic).
  * Synchronises `stream`. */

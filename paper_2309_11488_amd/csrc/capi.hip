@@ -1365,13 +1365,14 @@ static int class_parts(int mask) {
 // launches would fill (a burst of 24 requests of 10 000 to 200 000 cells on
 // four slots 4.91 against 4.41 ms).
 constexpr long long kFlowRowsMany = 200000, kFlowRowsTwo = 30000, kFlowRowsTwoF32 = 60000;
-static bool flow_size(const rs_ilu0 *M) {
+static bool flow_size(const rs_ilu0 *M, bool wells, bool tiles) {
     const int single = 1 << PC_LSWEEP | 1 << PC_USWEEP | 1 << PC_SPMV_V | 1 << PC_SPMV_T;
     const long long most = !M->an->sch.y_in ? kFlowRowsMany
                            : M->precision == RS_PREC_FP64 ? kFlowRowsTwo : kFlowRowsTwoF32;
-    return M->use_graph && M->fuse_spmv && !M->tile_sweeps && M->wdev.nw == 0 && !(g_prof.mask & single) &&
+    return M->use_graph && M->fuse_spmv && !tiles && !wells && !(g_prof.mask & single) &&
            (long long)M->n * M->batch <= most;
 }
+static bool flow_size(const rs_ilu0 *M) { return flow_size(M, M->wdev.nw > 0, M->tile_sweeps); }
 static bool flow_iteration(const rs_ilu0 *M) { return flow_size(M) && M->split() == 0; }
 // Workgroups of such a launch: as many as fit on the device at once (16
 // waves each, one a CU).
@@ -2258,14 +2259,16 @@ int rsolve_profile_get(int32_t cls, double *ms, int64_t *units, double *bytes) {
     return RS_OK;
 }
 
-static std::string tune_key(ilu0_t M) {
+// flow: the handle's iterations run their applications as one launch unless
+// the tuner's choice says otherwise (fmt 4; the kernels of earlier formats are gone).
+static std::string tune_key(ilu0_t M, bool flow) {
     int dev = 0;
     hipDeviceProp_t prop{};
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) prop.multiProcessorCount = 0;
     std::ostringstream k;
     k << "n=" << M->n << ",nnzb=" << M->nnzb << ",batch=" << M->batch << ",ord=" << M->an->sch.ordering
       << ",prec=" << M->precision << ",nl=" << M->an->sch.nl_levels << ",nu=" << M->an->sch.nu_levels
-      << ",m=" << M->an->sch.nnz_m << ",fmt=3"
+      << ",m=" << M->an->sch.nnz_m << ",fmt=4,path=" << (flow ? "one" : "many")
       << ",arch=" << prop.gcnArchName << ",cu=" << prop.multiProcessorCount;
     std::string r = k.str();
     for (char &c : r)
@@ -2287,7 +2290,8 @@ int ilu0_autotune(ilu0_t M, bcsr_t A, const double *b, int32_t mem, double reduc
     hipStream_t s = (hipStream_t)stream;
     rs_tune_result res{M->spmv_variant, M->sweep_variant, M->tile_sweeps ? 1 : 0, M->sweep_grid, 0.0, 0, 0,
                        M->reduce_split};
-    const std::string key = tune_key(M);
+    const bool flow = flow_size(M, A->nw > 0, false);
+    const std::string key = tune_key(M, flow);
     const char *cache = std::getenv("RSOLVE_TUNE_CACHE");
     if (cache && *cache) {
         std::ifstream in(cache);
@@ -2352,7 +2356,33 @@ int ilu0_autotune(ilu0_t M, bcsr_t A, const double *b, int32_t mem, double reduc
         return RS_OK;
     };
     const int sp0 = M->spmv_variant;
-    for (int v = 0; v < rs::RV_COUNT; ++v) {
+    if (flow) {
+        // the sweeps of an iteration are part of one launch, whatever their
+        // shape: that is timed on the call that takes it, an application
+        int sweep = M->sweep_variant;
+        double fastest = 1e300;
+        for (int v = 0; v < rs::RV_COUNT; ++v) {
+            apply({sp0, v, 0, M->sweep_grid, 0});
+            st = ilu0_apply(M, bb.as<double>(), xb.as<double>(), 0, M->batch, RS_MEM_DEVICE, stream);
+            if (st != RS_OK) return st;
+            HIP_TRY(hipStreamSynchronize(s));
+            const auto t0 = std::chrono::steady_clock::now();
+            for (int i = 0; i < reps; ++i) {
+                st = ilu0_apply(M, bb.as<double>(), xb.as<double>(), 0, M->batch, RS_MEM_DEVICE, stream);
+                if (st != RS_OK) return st;
+            }
+            HIP_TRY(hipStreamSynchronize(s));
+            const double us = std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count();
+            ++ncand;
+            if (us < fastest) {
+                fastest = us;
+                sweep = v;
+            }
+        }
+        st = time_cfg({sp0, sweep, 0, M->sweep_grid, 0});
+        if (st != RS_OK) return st;
+    }
+    for (int v = 0; !flow && v < rs::RV_COUNT; ++v) {
         st = time_cfg({sp0, v, 0, M->sweep_grid, 0});
         if (st != RS_OK) return st;
     }
@@ -2362,7 +2392,9 @@ int ilu0_autotune(ilu0_t M, bcsr_t A, const double *b, int32_t mem, double reduc
     }
     const Cfg sweep_best = bestc;
     for (int v = 0; v < rs::RV_COUNT; ++v) {
-        if (v == sp0) continue;
+        // one launch forms the product too: its shape would only group the
+        // partial sums
+        if (v == sp0 || (flow && sweep_best.tiles == 0)) continue;
         st = time_cfg({v, sweep_best.sweep, sweep_best.tiles, sweep_best.grid, 0});
         if (st != RS_OK) return st;
     }

@@ -418,3 +418,35 @@ def test_polled_reduction_recovers_from_a_wait_that_gives_up(method):
         for _ in range(3):
             got = solve()
             assert np.array_equal(got[0], want[0]) and got[1:] == want[1:]
+
+
+def test_tuning_knows_the_one_launch_iteration(tmp_path, monkeypatch):
+    """Where an iteration runs its applications as one launch the product's
+    shape cannot matter, so tuning leaves it; a choice saved by another
+    format, or by a handle whose iterations are separate launches, is not
+    taken."""
+    s = make_grid_system(16, 12, 8, seed=31)
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("RSOLVE_TUNE_CACHE", str(cache))
+    with rs.Solver(s.rowptr, s.colidx, s.vals, ordering=rs.ORDER_GRAPH_COLOUR) as sol:
+        sol.factor()
+        shape = rs.ilu0_get_option(sol.M, rs.OPT_SPMV_VARIANT)
+        for _ in range(4):
+            r = rs.ilu0_autotune(sol.M, sol.A, s.b[:, 0], reps=1)
+            assert r["from_cache"] == 0
+            if r["reduce_split"] == 0 and r["sweep_tiles"] == 0:
+                assert r["spmv_variant"] == shape
+            rs.ilu0_set_option(sol.M, rs.OPT_SPMV_VARIANT, shape)
+            rs.ilu0_set_option(sol.M, rs.OPT_SWEEP_TILES, 0)
+            rs.ilu0_set_option(sol.M, rs.OPT_REDUCE_SPLIT, 0)
+            saved = cache.read_text()
+            cache.unlink()
+        # a line of the format before this one with the split reduction
+        import re
+        key = re.sub("(fmt=[0-9]+)(,path=[a-z]+)?", "fmt=3", saved.split()[0])
+        cache.write_text(f"{key} 0 0 0 256 1 1.0\n")
+        assert rs.ilu0_autotune(sol.M, sol.A, s.b[:, 0], reps=1)["from_cache"] == 0
+        cache.write_text(saved)
+        assert rs.ilu0_autotune(sol.M, sol.A, s.b[:, 0], reps=1)["from_cache"] == 1
+        rs.ilu0_set_option(sol.M, rs.OPT_USE_GRAPH, 0)
+        assert rs.ilu0_autotune(sol.M, sol.A, s.b[:, 0], reps=1)["from_cache"] == 0
