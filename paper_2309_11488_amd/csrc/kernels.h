@@ -183,9 +183,12 @@ inline SpmvSums spmv_sums(int n, int waves, int split) {
 // Reduction scratch of a system whose largest launch has `blocks` workgroups.
 inline size_t part_stride_for(int blocks) { return 2 * (size_t)blocks + 2 * ((size_t)blocks / 32 + 1) + 16; }
 // Reduction counters sit on their own 128-byte lines (kTicketPad uint32
-// apart): counter 0 is the top of the tree, counter 1 + g that of group g.
+// apart): counter 0 is the top of the tree, counter 1 + g that of group g,
+// and behind those one for every 32 workgroups (one-wave workgroups).
 constexpr int kTicketPad = 32;
-inline size_t ticket_stride_for(int blocks) { return (size_t)kTicketPad * (2 + (size_t)blocks / 32 + 1); }
+inline size_t ticket_stride_for(int blocks) {
+    return (size_t)kTicketPad * (2 + (size_t)blocks / 32 + 1 + (size_t)blocks / 128 + 1);
+}
 inline size_t vec_stride(int n) { return (3 * (size_t)n + kVecTile - 1) / kVecTile * kVecTile; }
 int vec_blocks(int n);  // workgroups of the vector kernels for one padded vector
 

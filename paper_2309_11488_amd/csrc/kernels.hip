@@ -83,6 +83,56 @@ __device__ inline void block_sum(double (&v)[NV], double *lds) {
 // group g (one 128-byte line per counter, so groups do not contend).
 constexpr int kGroup = 32;
 
+// The ticket of workgroup bx on the counter of its group (groups of kGroup
+// PER workgroups): true in the last one to take it.  Larger groups count
+// kGroup workgroups at a time, on counters behind the groups' own, whose last
+// takers then take the group's: an atomic on one address takes about 10 ns,
+// and a one-wave workgroup holds its place until its ticket is back.  1M
+// cells, one wave a workgroup, non-temporal loads: a solve takes 2 272 us (FP32
+// factors 2 115); all 128 workgroups of a group on one counter and its
+// partials loaded one after another 2 322 (2 184); sums of 32 one-wave
+// partials, which are other bits than those of four waves, 2 259 (2 104).
+template <int PER>
+__device__ inline bool last_of_group(uint32_t *tickets, int nblk, int bx) {
+    constexpr int size = kGroup * PER;
+    const int g = bx / size, gsize = min(size, nblk - g * size);
+    auto last = [](uint32_t *c, int takers) {
+        return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(takers - 1);
+    };
+    uint32_t *group = tickets + (size_t)kTicketPad * (1 + g);
+    if constexpr (PER == 1) {
+        return last(group, gsize);
+    } else {
+        const int ng = (nblk + size - 1) / size, h = bx / kGroup;
+        uint32_t *sub = tickets + (size_t)kTicketPad * (1 + ng + h);
+        if (!last(sub, min(kGroup, nblk - h * kGroup))) return false;
+        __hip_atomic_store(sub, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return last(group, (gsize + kGroup - 1) / kGroup);
+    }
+}
+
+// The sums of group g over a wave, every load issued before the first is
+// used: the wave's workgroup holds up one-wave workgroups behind it.
+template <int NV, int PER>
+__device__ inline void group_sum(const double *part, int g, int gsize, double (&gs)[NV]) {
+    const int lane = threadIdx.x & 63;
+    const double *p = part + (size_t)g * (kGroup * PER * NV);
+    double x[PER][NV];
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            x[i][k] = __hip_atomic_load(p + min(lane * PER + i, gsize - 1) * NV + k, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) s += lane < kGroup && lane * PER + i < gsize ? x[i][k] : 0.0;
+        gs[k] = wave_sum(s);
+    }
+}
+
 template <int NV, int PER = 1>
 __device__ bool grid_reduce(double (&v)[NV], double *part, uint32_t *tickets, int nblk, int bx) {
     __shared__ double lds[16 * NV];
@@ -98,8 +148,7 @@ __device__ bool grid_reduce(double (&v)[NV], double *part, uint32_t *tickets, in
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_s_waitcnt(0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const uint32_t t = __hip_atomic_fetch_add(tickets + (size_t)kTicketPad * (1 + g), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        glast = t == (uint32_t)(gsize - 1);
+        glast = last_of_group<PER>(tickets, nblk, bx);
         last = 0;
     }
     __syncthreads();
@@ -108,15 +157,7 @@ __device__ bool grid_reduce(double (&v)[NV], double *part, uint32_t *tickets, in
         if (threadIdx.x < 64) {
             const int lane = threadIdx.x;
             double gs[NV];
-            for (int k = 0; k < NV; ++k) {
-                double p = 0.0;
-#pragma unroll
-                for (int i = 0; i < PER; ++i)
-                    if (lane < kGroup && lane * PER + i < gsize)
-                        p += __hip_atomic_load(part + (size_t)(g * size + lane * PER + i) * NV + k, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                gs[k] = wave_sum(p);
-            }
+            group_sum<NV, PER>(part, g, gsize, gs);
             if (lane == 0) {
                 __hip_atomic_store(tickets + (size_t)kTicketPad * (1 + g), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 for (int k = 0; k < NV; ++k)
@@ -175,22 +216,13 @@ __device__ void group_reduce(double (&v)[NV], double *part, uint32_t *tickets, i
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_s_waitcnt(0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const uint32_t t = __hip_atomic_fetch_add(tickets + (size_t)kTicketPad * (1 + g), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        glast = t == (uint32_t)(gsize - 1);
+        glast = last_of_group<PER>(tickets, nblk, bx);
     }
     __syncthreads();
     if (glast && threadIdx.x < 64) {
         const int lane = threadIdx.x;
         double gs[NV];
-        for (int k = 0; k < NV; ++k) {
-            double p = 0.0;
-#pragma unroll
-            for (int i = 0; i < PER; ++i)
-                if (lane < kGroup && lane * PER + i < gsize)
-                    p += __hip_atomic_load(part + (size_t)(g * size + lane * PER + i) * NV + k, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-            gs[k] = wave_sum(p);
-        }
+        group_sum<NV, PER>(part, g, gsize, gs);
         if (lane == 0) {
             __hip_atomic_store(tickets + (size_t)kTicketPad * (1 + g), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             for (int k = 0; k < NV; ++k) part[(size_t)nblk * NV + (size_t)g * NV + k] = gs[k];

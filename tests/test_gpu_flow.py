@@ -450,3 +450,25 @@ def test_tuning_knows_the_one_launch_iteration(tmp_path, monkeypatch):
         assert rs.ilu0_autotune(sol.M, sol.A, s.b[:, 0], reps=1)["from_cache"] == 1
         rs.ilu0_set_option(sol.M, rs.OPT_USE_GRAPH, 0)
         assert rs.ilu0_autotune(sol.M, sol.A, s.b[:, 0], reps=1)["from_cache"] == 0
+
+
+@pytest.mark.parametrize("n", [21, 671, 672, 673, 2687, 2688, 2689, 3381, 5377])
+def test_one_wave_products_count_their_groups(n):
+    """One-wave products at the edges of their counters (32 workgroups of 21
+    rows a counter, four counters a group): the sums of four waves, and the
+    counters cleared for the next launch."""
+    rowptr, colidx, vals = _pattern(f"chain_{n}")
+    b = np.random.default_rng(n).standard_normal((1, n, 3))
+    with rs.Solver(rowptr, colidx, vals, ordering=rs.ORDER_GRAPH_COLOUR) as sol:
+        rs.ilu0_set_option(sol.M, rs.OPT_USE_GRAPH, 0)        # separate launches
+        sol.factor()
+        for fuse in (1, 0):
+            rs.ilu0_set_option(sol.M, rs.OPT_FUSE_SPMV, fuse)
+            got = []
+            for variant in (0, 2, 8, 2):
+                rs.ilu0_set_option(sol.M, rs.OPT_SPMV_VARIANT, variant)
+                x, st, info = sol.solve(b, reduction=1e-9)
+                got.append((x, st, info[0]["half_steps"], info[0]["final_norm"], info[0]["true_rel_residual"]))
+            assert got[0][1] == rs.OK
+            for g in got[1:]:
+                assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:]
