@@ -149,7 +149,7 @@ static size_t instance_bytes(int32_t n, int32_t nnzb, int32_t precision) {
                + 8 * (10 * vec + 2 * 3 * N)          // Krylov vectors, sweep intermediate, staging
                + 8 * (2 * N / 21 + 8192)             // reduction partials
                + (1 << 20);                          // small buffers
-    if (precision == RS_PREC_FP32_FACTORS) b += 36 * Z + 8 * vec;   // second sweep intermediate (small systems)
+    if (precision == RS_PREC_FP32_FACTORS) b += 36 * Z;   // FP32 copies of the factors
     else b += 8 * 2 * vec;                           // lower parts of the second application (two-level patterns)
     return (size_t)b;
 }

@@ -147,3 +147,14 @@ def test_partition_rejects_bad_input():
     with pytest.raises(rs.RsolveError) as e:
         rs.bcsr_partition(s.rowptr, bad, 2)
     assert e.value.status == rs.BAD_PATTERN
+
+
+@pytest.mark.parametrize("n, nnzb", [(1, 1), (10_000, 67_000), (1_000_000, 6_940_000)])
+def test_request_footprint_counts_what_an_instance_holds(n, nnzb):
+    """FP32 factors are a copy of nine values a block (36 bytes) beyond the
+    FP64 ones; FP64 instances hold two vectors of lower parts instead.  The
+    second sweep vector of one-launch applications is no instance's: the
+    server solves with separate launches."""
+    vec = 3 * n + 1024
+    f32, f64 = (rs.Server.request_bytes(n, nnzb, p) for p in (rs.PREC_FP32_FACTORS, rs.PREC_FP64))
+    assert f32 - f64 == 36 * nnzb - 16 * vec
