@@ -907,15 +907,25 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kRo
 
 constexpr uint32_t kMark = 0x7ff4beefu;   // a NaN as FP32, and twice in a row as FP64
 
+// The bits of an entry: `word` may alias the floating-point type, whose entries
+// are also read and written as such, before and after, in the same kernels.
 template <typename T>
-struct FlowBits { using type = uint64_t; static constexpr uint64_t mark = ((uint64_t)kMark << 32) | kMark; };
+struct FlowBits {
+    using type = uint64_t;
+    typedef uint64_t __attribute__((may_alias)) word;
+    static constexpr uint64_t mark = ((uint64_t)kMark << 32) | kMark;
+};
 template <>
-struct FlowBits<float> { using type = uint32_t; static constexpr uint32_t mark = kMark; };
+struct FlowBits<float> {
+    using type = uint32_t;
+    typedef uint32_t __attribute__((may_alias)) word;
+    static constexpr uint32_t mark = kMark;
+};
 
 // An entry of a vector other rows of the launch write.
 template <typename T>
 __device__ inline typename FlowBits<T>::type flow_load(const T *p) {
-    return __hip_atomic_load((const typename FlowBits<T>::type *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load((const typename FlowBits<T>::word *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Store a row's result where other rows poll for it (never the mark itself).
@@ -924,12 +934,12 @@ __device__ inline void flow_store(T *p, T v) {
     using Bits = typename FlowBits<T>::type;
     Bits b = __builtin_bit_cast(Bits, v);
     if (b == FlowBits<T>::mark) b ^= 1;
-    __hip_atomic_store((Bits *)p, b, __ATOMIC_RELAXED, XCD ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((typename FlowBits<T>::word *)p, b, __ATOMIC_RELAXED,
+                       XCD ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
 }
 template <typename T>
 __device__ inline void flow_mark(T *p) {
-    using Bits = typename FlowBits<T>::type;
-    *(Bits *)p = FlowBits<T>::mark;
+    *(typename FlowBits<T>::word *)p = FlowBits<T>::mark;
 }
 
 // After a poll of a wave that found a mark: true when the wait gives up.
