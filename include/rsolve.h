@@ -105,7 +105,11 @@ enum rs_option {
     RS_OPT_USE_GRAPH = 3,    /* 1 (default): an iteration is captured once as a HIP graph and replayed.
                                 A capture is invalidated by device-synchronising calls (hipFree,
                                 synchronous copies) made meanwhile by other threads: set 0 when
-                                solving from several threads */
+                                solving from several threads.  0 also keeps systems of few rows
+                                from the one-launch applications (RS_OPT_FUSE_SPMV), whose
+                                waiting workgroups would hold compute units that the other
+                                threads' launches could use (with 1 such launches of several
+                                threads run side by side, slower, with the same results) */
     RS_OPT_PREDICT_POLL = 4, /* 1 (default): the first poll comes after as many iterations as the
                                 last converged solve on this handle needed, at most 50
                                 (iterations queued past convergence return at once); solves that
@@ -113,9 +117,11 @@ enum rs_option {
     RS_OPT_SPMV_VARIANT = 5, /* launch shape of the SpMVs: 0..8 = {4, 2, 1} waves per workgroup
                                 with blocks staged in LDS, then the same three reading directly,
                                 then the same three staged in LDS with non-temporal loads
-                                (default 0, from 10 000 rows on 2, from 250 000 on 8) */
+                                (default 0; from 250 000 rows of all systems on 2, or 8 when
+                                each system has as many) */
     RS_OPT_SWEEP_VARIANT = 6, /* launch shape of the one-launch-per-level sweeps (same encoding;
-                                default 2, from 250 000 rows on 8) */
+                                default 2, from 250 000 rows of a system on 8; bcsr_spmv's
+                                products start with the same shapes) */
     RS_OPT_REDUCE_SPLIT = 7, /* dot products fused into the SpMVs: 0 (default) = each workgroup
                                 joins a ticket tree inside the SpMV; 1 = each wave only stores
                                 its partial and a one-workgroup kernel adds them; 2 = each wave
@@ -141,9 +147,12 @@ enum rs_option {
                                 With separate wells (bcsr_set_wells), the well terms of those
                                 rows, which need the whole product's x, are subtracted after
                                 the SpMV by a small launch that also corrects the dot products.
-                                Systems of few rows (and no wells) run a whole application and
-                                its SpMV as one launch, whatever the pattern, with the same bits.
-                                Used with per-level sweeps and reduction split 0; 0: never */
+                                Systems of few rows (of all systems: up to 30 000 on patterns of
+                                RS_OPT_Y_INPUT_PATTERN, with FP32 factors 60 000, on others
+                                200 000; no wells) run a whole application and its SpMV as one
+                                launch, whatever the pattern, with the same bits (BiCGStab and
+                                GMRES, while RS_OPT_USE_GRAPH is on).
+                                Used with per-level sweeps and (BiCGStab) reduction split 0; 0: never */
     RS_OPT_FUSED_ROWS = 10,  /* read only (ilu0_get_option): how many rows the analysed pattern
                                 lets RS_OPT_FUSE_SPMV fuse (0: none) */
     RS_OPT_Y_INPUT = 11,     /* 1 (default): where the analysed pattern allows it (RS_OPT_Y_INPUT_PATTERN),
@@ -455,7 +464,8 @@ int ilu0_analyse_host(int32_t n_brows, const int32_t *row_ptr, const int32_t *co
  * launches), 2 = one upper sweep, 3 = one v = A phat launch, 4 = one
  * vector-update launch, 5 = one t = A shat launch (and GMRES's products
  * with A), 6 = one GMRES Gram-Schmidt launch, 7 = one preconditioner
- * application (both sweeps)).  Single-kernel units record dispatch events
+ * application (both sweeps; one launch with the product that follows it is
+ * one such unit, bytes included)).  Single-kernel units record dispatch events
  * (the kernel's own start and end); with graphs on, a timed sweep or
  * application replays as a graph segment of its own between two events.
  * Algorithmic bytes per unit (nL, nU: blocks of L and U; N rows; tb = 8

@@ -1374,8 +1374,9 @@ static bool flow_size(const rs_ilu0 *M, bool wells, bool tiles) {
 }
 static bool flow_size(const rs_ilu0 *M) { return flow_size(M, M->wdev.nw > 0, M->tile_sweeps); }
 static bool flow_iteration(const rs_ilu0 *M) { return flow_size(M) && M->split() == 0; }
-// Workgroups of such a launch: as many as fit on the device at once (16
-// waves each, one a CU).
+// Most workgroups of such a launch: those of large tiles (16 waves of up to
+// 128 registers a lane) are resident one a CU, those of small tiles (6 waves)
+// one or two; any further ones start as the first leave and find no ticket.
 constexpr int kFlowApplyGrid = 512;
 // The second y and the second reduction counters of such iterations,
 // allocated on first use (and kept).

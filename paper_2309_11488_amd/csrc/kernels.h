@@ -36,7 +36,7 @@ struct DevSchedule {
     // positions fuse_q0 + i of one upper level (0: no such rows)
     int fuse_n0, fuse_q0;
     int y_last;   // rows without upper blocks keep their y (Schedule::y_last)
-    // sweep tiles (see Schedule::Tiles)
+    // tiles of the single-launch sweeps (Schedule::ltiles, utiles)
     int nlt, nut;
     const int32_t *lt_start, *ut_start;
     // tiles of the single-launch application (Schedule::ApplyTiles)

@@ -472,3 +472,43 @@ def test_one_wave_products_count_their_groups(n):
             assert got[0][1] == rs.OK
             for g in got[1:]:
                 assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:]
+
+
+def test_two_threads_run_one_launch_applications_at_once():
+    """Two handles, two streams, two host threads, each with launches whose
+    workgroups wait on each other: every solve gives the bits it gives alone
+    (captures made before the threads start)."""
+    import threading
+    torch = pytest.importorskip("torch")
+    systems = [make_grid_system(23, 17, 11, active_frac=0.9, nnc_frac=0.03, seed=5), make_grid_system(40, 30, 20, seed=6)]
+    sols, want, fails = [], [], []
+    try:
+        for k, s in enumerate(systems):
+            st = torch.cuda.Stream()
+            sol = rs.Solver(s.rowptr, s.colidx, s.vals, ordering=rs.ORDER_GRAPH_COLOUR, stream=st.cuda_stream)
+            sols.append((sol, st, torch.from_numpy(np.ascontiguousarray(s.b[:, 0])).cuda()))
+            torch.cuda.synchronize()
+            sol.factor()
+            x = torch.empty_like(sols[k][2])
+            for _ in range(4):
+                sol.solve(sols[k][2], x, reduction=1e-6)
+            torch.cuda.synchronize()
+            want.append(x.cpu().numpy())
+
+        def work(k):
+            sol, _, b = sols[k]
+            x = torch.empty_like(b)
+            for _ in range(40):
+                if sol.solve(b, x, reduction=1e-6)[1] != rs.OK or not np.array_equal(x.cpu().numpy(), want[k]):
+                    fails.append(k)
+                    return
+
+        threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not fails
+    finally:
+        for sol, _, _ in sols:
+            sol.close()
