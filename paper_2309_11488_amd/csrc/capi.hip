@@ -236,7 +236,13 @@ struct rs_ilu0 {
     int precision = -1;
     bool factored = false;
     DevBuf pvals, L, U, Dinv, Lf, Uf, Dinvf, bad;
-    int32_t *bad_host = nullptr;   // the pivot record; pinned: a pageable copy costs a step of 4 000 cells 8 us more
+    // what a call reads from the device, in one pinned block (a pageable copy
+    // costs a step of 4 000 cells 8 us more): the states, the sweep counters
+    // and the pivot record
+    void *pinned = nullptr;
+    SysState *h_state = nullptr;
+    rs::SweepCtr *h_ctr = nullptr;
+    int32_t *bad_host = nullptr;
     // the last application queued without a host wait: the next call may use
     // another stream, and works in the same buffers
     hipEvent_t ev_apply = nullptr;
@@ -249,8 +255,6 @@ struct rs_ilu0 {
     // GMRES workspace: Krylov basis, per-system cycle state, reduction partials
     DevBuf gm_basis, gm_state, gm_part, gm_vpart;
     int last_gm_steps = 1;
-    SysState *h_state = nullptr;
-    rs::SweepCtr *h_ctr = nullptr;
     int chunk = 1;
     bool predict = true;       // first poll after as many iterations as the last converged solve needed
     int last_iters = 1;
@@ -328,9 +332,7 @@ struct rs_ilu0 {
         for (hipEvent_t e : {ev_f0, ev_f1, ev_s0, ev_s1, ev_apply})
             if (e) (void)hipEventDestroy(e);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
-        if (bad_host) (void)hipHostFree(bad_host);
-        if (h_state) (void)hipHostFree(h_state);
-        if (h_ctr) (void)hipHostFree(h_ctr);
+        if (pinned) (void)hipHostFree(pinned);
     }
 };
 
@@ -874,6 +876,19 @@ static int check_pair(ilu0_t M, bcsr_t A) {
     return RS_OK;
 }
 
+static int ensure_pinned(ilu0_t M) {
+    if (M->pinned) return RS_OK;
+    const size_t B = (size_t)M->batch;
+    static_assert(sizeof(rs::SweepCtr) % alignof(SysState) == 0, "the states follow the counters");
+    const size_t at_state = 2 * sizeof(rs::SweepCtr), at_bad = at_state + B * sizeof(SysState);
+    HIP_TRY(hipHostMalloc(&M->pinned, at_bad + B * sizeof(int32_t), hipHostMallocDefault));
+    unsigned char *p = (unsigned char *)M->pinned;
+    M->h_ctr = (rs::SweepCtr *)p;
+    M->h_state = (SysState *)(p + at_state);
+    M->bad_host = (int32_t *)(p + at_bad);
+    return RS_OK;
+}
+
 constexpr int kFlowFactorRows = 12000;   // see ilu0_factor
 
 int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *bad_row) {
@@ -896,7 +911,7 @@ int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *ba
         HIP_TRY(M->Dinvf.alloc(B * M->n * 9 * sizeof(float)));
     }
     M->factored = false;
-    if (!M->bad_host) HIP_TRY(hipHostMalloc((void **)&M->bad_host, B * sizeof(int32_t), hipHostMallocDefault));
+    if ((st = ensure_pinned(M)) != RS_OK) return st;
     if (!M->ev_f0) HIP_TRY(hipEventCreate(&M->ev_f0));
     if (!M->ev_f1) HIP_TRY(hipEventCreate(&M->ev_f1));
     HIP_TRY(hipEventRecord(M->ev_f0, s));
@@ -1045,6 +1060,8 @@ static int ensure_wells(ilu0_t M, const rs_bcsr *A, hipStream_t s) {
 // Allocate (first call) and bind the solve workspace; initialisation is
 // ordered on the caller's stream `s`.
 static int ensure_workspace(ilu0_t M, hipStream_t s) {
+    const int pin = ensure_pinned(M);
+    if (pin != RS_OK) return pin;
     const size_t B = (size_t)M->batch, vs = rs::vec_stride(M->n);
     const size_t vec = std::max<size_t>(B * vs, 1);
     if (!M->work.p) {
@@ -1066,8 +1083,8 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
     if (!M->state.p) {
         HIP_TRY(M->state.alloc(B * sizeof(SysState)));
         HIP_TRY(hipMemsetAsync(M->state.p, 0, B * sizeof(SysState), s));
-        HIP_TRY(hipHostMalloc((void **)&M->h_state, B * sizeof(SysState), hipHostMallocDefault));
-        HIP_TRY(hipHostMalloc((void **)&M->h_ctr, 2 * sizeof(rs::SweepCtr), hipHostMallocDefault));
+    }
+    if (!M->ctrs.p) {
         HIP_TRY(M->ctrs.alloc(2 * sizeof(rs::SweepCtr)));
         HIP_TRY(hipMemsetAsync(M->ctrs.p, 0, 2 * sizeof(rs::SweepCtr), s));
     }
