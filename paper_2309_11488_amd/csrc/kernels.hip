@@ -2289,14 +2289,12 @@ __device__ inline void sum_products(const double *__restrict__ p, int np, const 
 // workgroups; they are bounded all the same (`spin` polls, RS_OPT_SPIN_LIMIT).
 // A poll that gives up sets the system's gave_up, which the host answers by
 // marking every partial anew once the stream has drained (a partial that
-// comes late must not pass for a later reduction's), and gives NaN, which
-// ends the system's solve.  A half- or full-step update of 4 000 cells
+// comes late must not pass for a later reduction's); the mark in its place, a
+// NaN, ends the system's solve.  A half- or full-step update of 4 000 cells
 // takes 8.3 instead of 9.8 us, of 96k cells 9.1 instead of 10.7.
 template <int NV>
 __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx, int spin, SysState &S) {
     __shared__ double lds[16 * NV];
-    __shared__ int gave_up;
-    if (threadIdx.x == 0) gave_up = 0;
     block_sum<NV>(v, lds);
     if (threadIdx.x == 0)
         for (int k = 0; k < NV; ++k) flow_store<false>(part + (size_t)bx * NV + k, v[k]);
@@ -2317,7 +2315,7 @@ __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx, int
                 for (int k = 0; k < NV; ++k) miss |= t[u][k] == FlowBits<double>::mark;
             if (!__any(miss)) break;
             if (spins >= spin) {
-                gave_up = 1;
+                S.gave_up = 1;
                 break;
             }
             asm volatile("" ::: "memory");
@@ -2335,13 +2333,6 @@ __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx, int
         }
     }
     __syncthreads();   // every thread has read its partials
-    if (gave_up) {
-        if (threadIdx.x == 0) {
-            S.gave_up = 1;
-            for (int k = 0; k < NV; ++k) v[k] = __builtin_nan("");
-        }
-        return true;
-    }
     for (int e = threadIdx.x; e < nblk * NV; e += blockDim.x) flow_mark(part + e);
     if (threadIdx.x < 64) {
         const int ng = (nblk + kGroup - 1) / kGroup;
