@@ -879,8 +879,8 @@ static int check_pair(ilu0_t M, bcsr_t A) {
 static int ensure_pinned(ilu0_t M) {
     if (M->pinned) return RS_OK;
     const size_t B = (size_t)M->batch;
-    static_assert(sizeof(rs::SweepCtr) % alignof(SysState) == 0, "the states follow the counters");
-    const size_t at_state = 2 * sizeof(rs::SweepCtr), at_bad = at_state + B * sizeof(SysState);
+    auto after = [](size_t at, size_t bytes) { return (at + bytes + 255) / 256 * 256; };
+    const size_t at_state = after(0, 2 * sizeof(rs::SweepCtr)), at_bad = after(at_state, B * sizeof(SysState));
     HIP_TRY(hipHostMalloc(&M->pinned, at_bad + B * sizeof(int32_t), hipHostMallocDefault));
     unsigned char *p = (unsigned char *)M->pinned;
     M->h_ctr = (rs::SweepCtr *)p;
