@@ -250,6 +250,7 @@ struct rs_ilu0 {
     bool apply_queued = false;
     // solve workspace
     DevBuf work, ywork, ywork2, ftickets, vpart, part, spart, fpart, tickets, state, bstage, xstage, ctrs, fctr;
+    bool no_flow = false;      // no room for what one-launch applications need besides
     bool y_marked = false;     // ywork holds the mark everywhere (single-launch sweeps)
     Krylov k{};
     // GMRES workspace: Krylov basis, per-system cycle state, reduction partials
@@ -1386,7 +1387,7 @@ static bool flow_size(const rs_ilu0 *M, bool wells, bool tiles) {
     const int single = 1 << PC_LSWEEP | 1 << PC_USWEEP | 1 << PC_SPMV_V | 1 << PC_SPMV_T;
     const long long most = !M->an->sch.y_in ? kFlowRowsMany
                            : M->precision == RS_PREC_FP64 ? kFlowRowsTwo : kFlowRowsTwoF32;
-    return M->use_graph && M->fuse_spmv && !tiles && !wells && !(g_prof.mask & single) &&
+    return M->use_graph && M->fuse_spmv && !M->no_flow && !tiles && !wells && !(g_prof.mask & single) &&
            (long long)M->n * M->batch <= most;
 }
 static bool flow_size(const rs_ilu0 *M) { return flow_size(M, M->wdev.nw > 0, M->tile_sweeps); }
@@ -1396,12 +1397,20 @@ static bool flow_iteration(const rs_ilu0 *M) { return flow_size(M) && M->split()
 // one or two; any further ones start as the first leave and find no ticket.
 constexpr int kFlowApplyGrid = 512;
 // The second y and the second reduction counters of such iterations,
-// allocated on first use (and kept).
-static int ensure_flow(ilu0_t M, hipStream_t s) {
-    if (M->ftickets.p) return RS_OK;
+// allocated on first use (and kept).  Where they do not fit the device, the
+// handle keeps to the separate launches, which need neither.
+static int ensure_flow(ilu0_t M, hipStream_t s, bool &flow) {
+    if (!flow || M->ftickets.p) return RS_OK;
     const size_t tb = (size_t)M->batch * M->k.fticket_stride * sizeof(uint32_t);
-    HIP_TRY(M->ywork2.alloc(std::max<size_t>((size_t)M->batch * rs::vec_stride(M->n), 1) * sizeof(double)));
-    HIP_TRY(M->ftickets.alloc(tb));
+    hipError_t e = M->ywork2.alloc(std::max<size_t>((size_t)M->batch * rs::vec_stride(M->n), 1) * sizeof(double));
+    if (e == hipSuccess) e = M->ftickets.alloc(tb);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        M->no_flow = true;
+        flow = false;
+        return RS_OK;
+    }
+    HIP_TRY(e);
     HIP_TRY(hipMemsetAsync(M->ftickets.p, 0, tb, s));
     M->k.y2 = M->ywork2.p;
     M->k.ftickets = M->ftickets.as<uint32_t>();
@@ -1702,7 +1711,7 @@ int ilu0_apply(ilu0_t M, const double *v, double *z, int32_t first_sys, int32_t 
     if (mem != RS_MEM_DEVICE) HIP_TRY(hipMemcpyAsync(z, zd, m * sizeof(double), hipMemcpyDeviceToHost, s));
     // Only single-launch sweeps leave a word to read, and host vectors need
     // the copy's end; a device caller's stream goes on without the host
-    // (200 000 cells, an application and a product: 95 -> 70 us).  An event
+    // (200 000 cells, an application and a product: 99 -> 74 us).  An event
     // keeps the handle's next call behind this one.  The one application of a
     // factorisation that fills in U waits for it, so that other streams (and
     // captures, which cannot wait for the event) find it in place.
@@ -1854,12 +1863,9 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
     if (st != RS_OK) return st;
     st = ensure_wells(M, A, s);
     if (st != RS_OK) return st;
-    const bool flow = flow_iteration(M);
-    if (flow) {
-        if ((st = ensure_flow(M, s)) != RS_OK) return st;
-    } else if (reads_u(M, fused_iteration(M)) && (st = ensure_u(M, s)) != RS_OK) {
-        return st;
-    }
+    bool flow = flow_iteration(M);
+    if ((st = ensure_flow(M, s, flow)) != RS_OK) return st;
+    if (!flow && reads_u(M, fused_iteration(M)) && (st = ensure_u(M, s)) != RS_OK) return st;
     if (lower_parts_iteration(M) && (st = ensure_lower_parts(M, s)) != RS_OK) return st;
     const size_t m = 3 * (size_t)M->n * B;
     const double *bd = nullptr;
@@ -2115,11 +2121,8 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
     if (st != RS_OK) return st;
     GmFlow flow;
     flow.on = flow_size(M);
-    if (flow.on) {
-        if ((st = ensure_flow(M, s)) != RS_OK) return st;
-    } else if (reads_u(M, false) && (st = ensure_u(M, s)) != RS_OK) {
-        return st;
-    }
+    if ((st = ensure_flow(M, s, flow.on)) != RS_OK) return st;
+    if (!flow.on && reads_u(M, false) && (st = ensure_u(M, s)) != RS_OK) return st;
     Krylov &k = M->k;
     // basis: restart columns (the column a cycle's last step would add is
     // never used); zeroed once, so the padding of every column stays zero
