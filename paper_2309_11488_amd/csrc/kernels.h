@@ -142,13 +142,12 @@ enum RowVariant { RV_W4_LDS = 0, RV_W2_LDS = 1, RV_W1_LDS = 2, RV_W4_DIRECT = 3,
 // Non-temporal loads of the blocks pay once the vectors outgrow the L2s: 280k
 // cells with NNCs 700 against 757 us a solve, 1M cells 2.24 against 2.39 ms,
 // but 120k cells 333 against 319.  Products take one wave from 250 000 rows of
-// all systems on (a step of 1M cells 3.00 against 3.02 ms, of 64 systems of
-// 48 000 cells 5.64 against 5.76); below, their workgroups are few and the
-// tickets of their partials weigh more (50 000 cells with wells 385 against
-// 398 us).  The partials are those of four waves either way (sum_per): another
-// order changes the last bits of alpha and omega, which an ill-conditioned
-// system (one in a dozen of 50 000 cells with strong wells) carries into
-// digits of x.
+// all systems on (a solve of 1M cells 2.27 against 2.36 ms, of 64 systems of
+// 48 000 cells 3.78 against 3.95); below nothing is gained (50 000 cells with
+// wells 375 us either way).  The partials are those of four waves either way
+// (sum_per): another order changes the last bits of alpha and omega, which an
+// ill-conditioned system (one in a dozen of 50 000 cells with strong wells)
+// carries into digits of x.
 inline int default_sweep_variant(int n) { return n >= 250000 ? RV_W1_LDS_NT : RV_W1_LDS; }
 inline int default_spmv_variant(int n, int batch) {
     return (double)n * batch >= 250000.0 ? default_sweep_variant(n) : RV_W4_LDS;

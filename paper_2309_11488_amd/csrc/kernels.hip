@@ -2290,8 +2290,9 @@ __device__ inline void sum_products(const double *__restrict__ p, int np, const 
 // A poll that gives up sets the system's gave_up, which the host answers by
 // marking every partial anew once the stream has drained (a partial that
 // comes late must not pass for a later reduction's); the mark in its place, a
-// NaN, ends the system's solve.  A half- or full-step update of 4 000 cells
-// takes 8.3 instead of 9.8 us, of 96k cells 9.1 instead of 10.7.
+// NaN, ends the system's solve.  A half- and a full-step
+// update of 4 000 cells take 6.8 and 7.9 us instead of 8.1 and 9.4, of 96k
+// cells 6.9 and 9.7 instead of 8.2 and 10.5.
 template <int NV>
 __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx, int spin, SysState &S) {
     __shared__ double lds[16 * NV];
