@@ -974,6 +974,7 @@ int ilu0_factor(ilu0_t M, bcsr_t A, int32_t precision, void *stream, int32_t *ba
     if (M->factor_async) return RS_OK;
     HIP_TRY(hipMemcpyAsync(M->bad_host, M->bad.p, B * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    M->apply_queued = false;   // `s` came after it
     return factor_result(M, bad_row);
 }
 
@@ -1894,6 +1895,7 @@ int bicgstab_solve(ilu0_t M, bcsr_t A, const double *b, double *x, double reduct
         if (M->tile_sweeps || flow) HIP_TRY(hipMemcpyAsync(M->h_ctr, k.lctr, 2 * sizeof(rs::SweepCtr), hipMemcpyDeviceToHost, s));
         if (mem != RS_MEM_DEVICE) HIP_TRY(hipMemcpyAsync(x, xd, m * sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
+        M->apply_queued = false;   // `s` came after it
         return RS_OK;
     };
     auto all_done = [&]() {
@@ -2184,6 +2186,7 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         if (M->tile_sweeps || flow.on) HIP_TRY(hipMemcpyAsync(M->h_ctr, k.lctr, 2 * sizeof(rs::SweepCtr), hipMemcpyDeviceToHost, s));
         if (mem != RS_MEM_DEVICE) HIP_TRY(hipMemcpyAsync(x, xd, m * sizeof(double), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
+        M->apply_queued = false;   // `s` came after it
         return RS_OK;
     };
     auto done_all = [&]() {
