@@ -2363,8 +2363,13 @@ int ilu0_autotune(ilu0_t M, bcsr_t A, const double *b, int32_t mem, double reduc
     int ncand = 0;
     auto time_cfg = [&](const Cfg &c) -> int {
         apply(c);
-        int r = bicgstab_solve(M, A, bb.as<double>(), xb.as<double>(), reduction, 200, RS_MEM_DEVICE, stream, nullptr);
-        if (r < 0) return r;
+        // the first solve of a handle learns how many iterations to queue, the
+        // second captures graphs of as many
+        int r = 0;
+        for (int i = 0; i < 2; ++i) {
+            r = bicgstab_solve(M, A, bb.as<double>(), xb.as<double>(), reduction, 200, RS_MEM_DEVICE, stream, nullptr);
+            if (r < 0) return r;
+        }
         const auto t0 = std::chrono::steady_clock::now();
         for (int i = 0; i < reps; ++i) {
             r = bicgstab_solve(M, A, bb.as<double>(), xb.as<double>(), reduction, 200, RS_MEM_DEVICE, stream, nullptr);
