@@ -149,7 +149,8 @@ enum rs_option {
                                 the SpMV by a small launch that also corrects the dot products.
                                 Systems of few rows (of all systems: up to 30 000 on patterns of
                                 RS_OPT_Y_INPUT_PATTERN, with FP32 factors 60 000, on others
-                                200 000; no wells) run a whole application and its SpMV as one
+                                200 000; at most 512 sweep levels; no wells) run a whole
+                                application and its SpMV as one
                                 launch, whatever the pattern, with the same bits (BiCGStab and
                                 GMRES, while RS_OPT_USE_GRAPH is on).
                                 Used with per-level sweeps and (BiCGStab) reduction split 0; 0: never */

@@ -1382,13 +1382,19 @@ static int class_parts(int mask) {
 // with FP32 factors.  Not with RS_OPT_USE_GRAPH off, which says that other
 // threads solve meanwhile: waiting workgroups hold CUs that the others'
 // launches would fill (a burst of 24 requests of 10 000 to 200 000 cells on
-// four slots 4.91 against 4.41 ms).
+// four slots 4.91 against 4.41 ms).  Not on schedules of more than kFlowLevels
+// levels either: every level is a hop that all waiting workgroups poll
+// through, over all XCDs, and such schedules have the single-launch sweeps
+// (RS_OPT_SWEEP_TILES, their default), which run on one.  A 7-point grid of
+// 200 000 rows has up to 300 levels under RCM.
+constexpr int kFlowLevels = 512;
 constexpr long long kFlowRowsMany = 200000, kFlowRowsTwo = 30000, kFlowRowsTwoF32 = 60000;
 static bool flow_size(const rs_ilu0 *M, bool wells, bool tiles) {
     const int single = 1 << PC_LSWEEP | 1 << PC_USWEEP | 1 << PC_SPMV_V | 1 << PC_SPMV_T;
     const long long most = !M->an->sch.y_in ? kFlowRowsMany
                            : M->precision == RS_PREC_FP64 ? kFlowRowsTwo : kFlowRowsTwoF32;
-    return M->use_graph && M->fuse_spmv && !M->no_flow && !tiles && !wells && !(g_prof.mask & single) &&
+    const rs::Schedule &S = M->an->sch;
+    return M->use_graph && M->fuse_spmv && !M->no_flow && std::max(S.nl_levels, S.nu_levels) <= kFlowLevels && !tiles && !wells && !(g_prof.mask & single) &&
            (long long)M->n * M->batch <= most;
 }
 static bool flow_size(const rs_ilu0 *M) { return flow_size(M, M->wdev.nw > 0, M->tile_sweeps); }

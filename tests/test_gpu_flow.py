@@ -512,3 +512,24 @@ def test_two_threads_run_one_launch_applications_at_once():
     finally:
         for sol, _, _ in sols:
             sol.close()
+
+
+@pytest.mark.parametrize("n", [512, 513])
+def test_deep_schedules_keep_separate_launches(n):
+    """A chain under reverse Cuthill-McKee has a level a row: up to 512 levels
+    an iteration's applications are one launch each, beyond it stays separate
+    launches; the bits of graphs off either way."""
+    rowptr, colidx, vals = _pattern(f"chain_{n}")
+    b = np.random.default_rng(n).standard_normal((1, n, 3))
+    with rs.Solver(rowptr, colidx, vals, ordering=rs.ORDER_RCM_LEVEL_SET) as s:
+        rs.ilu0_set_option(s.M, rs.OPT_SWEEP_TILES, 0)
+        s.factor()
+        assert rs.ilu0_get_sweep_levels(s.M)[0] == n
+        got = []
+        for graph in (0, 1, 1):
+            rs.ilu0_set_option(s.M, rs.OPT_USE_GRAPH, graph)
+            x, st, info = s.solve(b, reduction=1e-9)
+            got.append((x, st, info[0]["half_steps"], info[0]["final_norm"], info[0]["true_rel_residual"]))
+    assert got[0][1] == rs.OK
+    for g in got[1:]:
+        assert np.array_equal(g[0], got[0][0]) and g[1:] == got[0][1:]
