@@ -1105,7 +1105,7 @@ static int ensure_workspace(ilu0_t M, hipStream_t s) {
     k.y = M->ywork.p;
     k.y2 = M->ywork2.p;
     k.ftickets = M->ftickets.as<uint32_t>();
-    k.fticket_stride = rs::ticket_stride_for(rs::fuse_blocks(M->an->sch.fuse_n0, 1));
+    k.fticket_stride = (uint32_t)rs::ticket_stride_for(rs::fuse_blocks(M->an->sch.fuse_n0, 1));
     k.part = M->part.as<double>();
     k.part_stride = pstride;
     k.tickets = M->tickets.as<uint32_t>();
@@ -2148,8 +2148,8 @@ int gmres_solve(ilu0_t M, bcsr_t A, const double *b, double *x, int32_t restart,
         HIP_TRY(hipGetLastError());
     }
     rs::GmWork g{M->gm_basis.as<double>(), colstride, k.vstride, M->gm_part.as<double>(), rs::gm_part_stride(),
-                 k.tickets, k.ticket_stride, M->gm_vpart.as<double>(), M->gm_state.as<rs::GmState>(), k.st,
-                 M->spin_limit};
+                 k.tickets, (uint32_t)k.ticket_stride, M->spin_limit, M->gm_vpart.as<double>(), M->gm_state.as<rs::GmState>(),
+                 k.st};
     const size_t m = 3 * (size_t)M->n * B;
     const double *bd = nullptr;
     st = stage_in(b, mem, M->bstage, m, s, &bd);

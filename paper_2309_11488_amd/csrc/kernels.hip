@@ -2292,7 +2292,7 @@ __device__ inline void sum_products(const double *__restrict__ p, int np, const 
 // comes late must not pass for a later reduction's); the mark in its place, a
 // NaN, ends the system's solve.  A half- and a full-step
 // update of 4 000 cells take 6.8 and 7.9 us instead of 8.1 and 9.4, of 96k
-// cells 6.9 and 9.7 instead of 8.2 and 10.5.
+// cells 6.8 and 9.6 instead of 8.2 and 10.5.
 template <int NV>
 __device__ bool poll_reduce(double (&v)[NV], double *part, int nblk, int bx, int spin, SysState &S) {
     __shared__ double lds[16 * NV];
@@ -2648,7 +2648,7 @@ constexpr int kGmThreads = 256;
 template <int NV>
 __device__ inline bool gm_reduce(double (&v)[NV], const GmWork &g, int sys, int nblk, int bx) {
     if (nblk <= kGmPollBlocks) return poll_reduce<NV>(v, g.vpart + sys * gm_poll_stride(), nblk, bx, g.spin, g.st[sys]);
-    return grid_reduce<NV>(v, g.part + sys * g.pstride, g.tickets + sys * g.tkstride, nblk, bx);
+    return grid_reduce<NV>(v, g.part + sys * g.pstride, g.tickets + (size_t)sys * g.tkstride, nblk, bx);
 }
 
 __device__ inline void gm_cycle_start(GmState &G, double beta) {
